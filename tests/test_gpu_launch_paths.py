@@ -1,0 +1,39 @@
+"""Kernels and launch rules at the sizes where they can go wrong."""
+import numpy as np
+import pytest
+
+from tests import moments_ref as R
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def phx():
+    from paper_1504_06570_amd import phx
+    return phx
+
+
+EDGE = (1 << 127) - 1
+
+
+@pytest.mark.parametrize("n_src", [1, 8, 9, 441])
+def test_moments_at_the_edges_of_their_words(phx, n_src):
+    """Counts of one and of 64 bits, sums of zero, of one bit, of full range and either sign, exact
+    halves, against rational arithmetic (equal: each result is one rounding of an exact ratio)."""
+    import torch
+    from paper_1504_06570_amd.scene import configs as C
+    rng = np.random.default_rng(n_src)
+    edge = [(1, 1, -1, 1, 0, -1), ((1 << 64) - 1, EDGE, -EDGE - 1, -EDGE - 1, EDGE, 1),
+            (0, 5, 5, 5, 5, 5), (2, (1 << 54) + 1, -((1 << 54) + 1), 1, 1, 1),
+            (3, EDGE, EDGE, EDGE, 1 << 126, -(1 << 126))]
+    sums = edge[:n_src]
+    while len(sums) < n_src:
+        n = int(rng.integers(1, 10 ** 7))
+        x, y = (int(v) for v in rng.normal(0.0, 3e-2, 2) * 2.0 ** 44)
+        d = [int(v) for v in rng.integers(-n, n, 2)]
+        sums.append((n, n * x + d[0], n * y + d[1], n * (x * x + 10 ** 17), n * (y * y + 10 ** 17),
+                     n * (x * y + 10 ** 15)))
+    tr = phx.Tracer(C.tiny(scale=0.01))
+    w = torch.from_numpy(R.words_of(sums)).cuda()
+    got = tr.moments(w).cpu().numpy()
+    np.testing.assert_array_equal(got, R.moments_from_sums(sums))
