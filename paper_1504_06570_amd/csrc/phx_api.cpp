@@ -79,6 +79,7 @@ struct phx_ctx_s {
     hipStream_t cap_stream = nullptr;
     hipStream_t aux_stream = nullptr;       // optics stage of the chunk pipeline
     std::vector<hipEvent_t> pipe_ev;        // hand-off events of the chunk pipeline
+    hipEvent_t order_ev = nullptr;          // end of the context's last launch (see order_begin)
     std::map<std::string, hipGraphExec_t> graphs;
     float autotune_ms = 0.0f;
     // adjoint workspace
@@ -471,6 +472,7 @@ void phx_destroy(phx_ctx c) {
     if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
     if (c->aux_stream) (void)hipStreamDestroy(c->aux_stream);
     for (hipEvent_t e : c->pipe_ev) (void)hipEventDestroy(e);
+    if (c->order_ev) (void)hipEventDestroy(c->order_ev);
     for (hipEvent_t e : c->ev_pool) (void)hipEventDestroy(e);
     delete c;
 }
@@ -1199,11 +1201,33 @@ uint64_t make_plan(phx_ctx c, const phx_trace_args* a, const phx::Launch& L, uin
     return n;
 }
 
+// Launches of one context share its workspace, so a launch waits for the one before it, whichever
+// stream that was on: order_end records an event behind a launch and order_begin makes the next
+// launch's stream wait for it (free on the same stream; the record takes the host 4 us).  A stream
+// that is being captured does neither: its launches run when the graph does.
+bool capturing(hipStream_t st) {
+    hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(st, &s) == hipSuccess && s != hipStreamCaptureStatusNone;
+}
+phx_status order_begin(phx_ctx c, hipStream_t st) {
+    if (!c->order_ev || capturing(st)) return PHX_OK;
+    const hipError_t e = hipStreamWaitEvent(st, c->order_ev, 0);
+    return e == hipSuccess ? PHX_OK : hip_fail(c, e, "hipStreamWaitEvent");
+}
+phx_status order_end(phx_ctx c, hipStream_t st) {
+    if (capturing(st)) return PHX_OK;
+    hipError_t e = hipSuccess;
+    if (!c->order_ev) e = hipEventCreateWithFlags(&c->order_ev, hipEventDisableTiming);
+    if (e == hipSuccess) e = hipEventRecord(c->order_ev, st);
+    return e == hipSuccess ? PHX_OK : hip_fail(c, e, "hipEventRecord");
+}
+
 // Validation, uploads and workspace for a trace; fills the launch description.  May synchronise
 // `st` (new prefix table, growing workspace, changed parameter block).
 phx_status prepare(phx_ctx c, const phx_trace_args* a, hipStream_t st, phx::Launch& L,
                    phx::Workspace& W, bool need_image = true) {
     phx_status r = validate_launch(c, a, L, need_image);
+    if (r == PHX_OK) r = order_begin(c, st);
     if (r != PHX_OK) return r;
     if (a->photon_count == 0) {
         std::vector<uint64_t> pre(L.n_src + 1, 0);
@@ -1378,8 +1402,8 @@ phx_status phx_trace(phx_ctx c, const phx_trace_args* a, void* stream) {
     phx::Launch L;
     phx::Workspace W;
     phx_status r = prepare(c, a, st, L, W);
-    if (r != PHX_OK) return r;
-    return enqueue(c, L, W, st, true);
+    if (r == PHX_OK) r = enqueue(c, L, W, st, true);
+    return r == PHX_OK ? order_end(c, st) : r;
 }
 
 phx_status phx_trace_noalloc(phx_ctx c, const phx_trace_args* a, void* stream) {
@@ -1481,7 +1505,7 @@ phx_status phx_trace_batched(phx_ctx c, const phx_trace_args* a, void* stream) {
     }
     hipError_t e = hipGraphLaunch(it->second, st);
     if (e != hipSuccess) return hip_fail(c, e, "hipGraphLaunch");
-    return PHX_OK;
+    return order_end(c, st);
 }
 
 phx_status phx_adjoint(phx_ctx c, const phx_trace_args* a, const double* seed_dev,
@@ -1556,7 +1580,7 @@ phx_status phx_adjoint(phx_ctx c, const phx_trace_args* a, const double* seed_de
     hipError_t e = phx::launch_adjoint(c->dparams, L, W, c->n_cu, c->cfg, A, c->d_colsum, grad_dev,
                                        st, pipe_of(c), T);
     if (e != hipSuccess) return hip_fail(c, e, "adjoint kernel launch");
-    return PHX_OK;
+    return order_end(c, st);
 }
 
 phx_status phx_adjoint_moments(phx_ctx c, const phx_trace_args* a, const uint64_t* moments_dev,

@@ -2668,7 +2668,10 @@ struct Stages {
     hipStream_t stream;
     const Pipe& pipe;
     const Timing& T;
-    bool piped() const { return pipe.aux && pipe.ev; }
+    // A launch of one chunk has nothing to overlap: its stages stay on the caller's stream (each
+    // hand-off between the streams costs 10-12 us; 1e5 photons through the paraboloid 68 us with
+    // them, 27 us without).
+    bool piped() const { return pipe.aux && pipe.ev && W.n_plan > 1; }
     // events per chunk: 0 pre-roll done, 1 sky done, 2 optics done; then one fork event
     hipEvent_t ev(int kind, uint64_t c) const { return pipe.ev[3 * c + kind]; }
     void mark(int kind, int edge, hipStream_t s) const {

@@ -37,3 +37,26 @@ def test_moments_at_the_edges_of_their_words(phx, n_src):
     w = torch.from_numpy(R.words_of(sums)).cuda()
     got = tr.moments(w).cpu().numpy()
     np.testing.assert_array_equal(got, R.moments_from_sums(sums))
+
+
+def test_launches_of_one_context_on_two_streams_wait_for_each_other(phx):
+    """One-chunk launches stay on the caller's stream; two streams used in turn must not meet in the
+    context's workspace: the images add up to those of one stream."""
+    import torch
+    from paper_1504_06570_amd.scene import configs as C
+    scene = C.full(scale=2e-4, screen_n=128)
+    tr = phx.Tracer(scene)
+    flags = int(scene.physics) | phx.F_CULL
+    want = tr.trace(flags=flags)[0]
+    for k in range(5):
+        tr.trace(want, flags=flags, seed=100 + k)
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    images = [tr.new_image(), tr.new_image()]
+    torch.cuda.synchronize()
+    tr.trace(images[0], flags=flags, stream=streams[0])
+    for k in range(5):
+        tr.trace(images[(k + 1) % 2], flags=flags, seed=100 + k, stream=streams[(k + 1) % 2])
+    torch.cuda.synchronize()
+    assert torch.equal(images[0] + images[1], want)
+    tr.close()
