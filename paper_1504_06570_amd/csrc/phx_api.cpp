@@ -153,6 +153,16 @@ void free_dev(T*& p) {
     p = nullptr;
 }
 
+// The smallest double s >= 0 with sqrt(s) >= r (the rounded square root does not decrease), so that
+// sqrt(x) < r exactly when x < s.
+double sqrt_threshold(double r) {
+    if (!(r > 0.0)) return 0.0;
+    double s = r * r;
+    while (std::sqrt(s) >= r && s > 0.0) s = std::nextafter(s, 0.0);
+    while (std::sqrt(s) < r) s = std::nextafter(s, INFINITY);
+    return s;
+}
+
 // Rigid-body transforms of the surfaces from the perturbation vector.  A group's elements are
 // rotated by R = R_x(tx) R_y(ty) about the group's pivot P and translated by (dx, dy, dz): an
 // element-frame point q maps to g = R q + t with t = P + R (v - P) + d, v = (0, 0, z_vertex).
@@ -169,13 +179,16 @@ void build_surfaces(phx_ctx c) {
         d.coating = s.coating;
         d.c = s.curvature;
         d.kappa1 = 1.0 + s.conic;
-        d.asphere = 0;
+        d.kc2 = d.kappa1 * d.c * d.c;
+        bool even = false, odd = false;
         for (int i = 0; i < 8; ++i) {
             d.alpha[i] = s.alpha[i];
-            if (s.alpha[i] != 0.0) d.asphere = (i & 1) ? 1 : 2;   // alpha[i] is alpha_{i+3}
+            if (s.alpha[i] != 0.0) ((i & 1) ? even : odd) = true;   // alpha[i] is alpha_{i+3}
         }
-        for (int i = 0; i < 8; i += 2)
-            if (s.alpha[i] != 0.0) d.asphere = 2;                  // an odd power is present
+        d.bits = odd ? phx::kSurfGeneral : even ? phx::kSurfEven : 0u;
+        if (d.c == 0.0 && !odd && !even) d.bits |= phx::kSurfPlane;
+        if (s.kind == PHX_MIRROR) d.bits |= phx::kSurfMirror;
+        if (s.medium == PHX_GLASS) d.bits |= phx::kSurfGlass;
         d.r_in = s.r_inner;
         d.r_out = s.r_outer;
         d.z_vertex = s.z_vertex;
@@ -189,7 +202,8 @@ void build_surfaces(phx_ctx c) {
             dx = th[0]; dy = th[1]; tx = th[2]; ty = th[3]; dz = th[4];
             P = p.group_pivot[s.group];
         }
-        d.moved = (dx != 0 || dy != 0 || dz != 0 || tx != 0 || ty != 0) ? 1 : 0;
+        const bool moved = dx != 0 || dy != 0 || dz != 0 || tx != 0 || ty != 0;
+        if (moved) d.bits |= phx::kSurfMoved;
         const double cx = std::cos(tx), sx = std::sin(tx), cy = std::cos(ty), sy = std::sin(ty);
         // R_x(tx) R_y(ty)
         const double R[9] = {cy, 0.0, sy, sx * sy, cx, -sx * cy, -cx * sy, sx, cx * cy};
@@ -198,14 +212,15 @@ void build_surfaces(phx_ctx c) {
         for (int i = 0; i < 3; ++i) {
             const double rv = R[3 * i] * (v[0] - P[0]) + R[3 * i + 1] * (v[1] - P[1]) +
                               R[3 * i + 2] * (v[2] - P[2]);
-            d.t[i] = d.moved ? P[i] + rv + dd[i] : v[i];
+            d.t[i] = moved ? P[i] + rv + dd[i] : v[i];
         }
+        d.tz = d.t[2];
         for (int i = 0; i < 9; ++i) d.R[i] = R[i];
     }
     // medium in front of each surface, in travel order (mirrors keep it, lenses set it)
     bool glass = false;
     for (int k = 0; k < p.n_surfaces; ++k) {
-        H.surf[k].glass_in = glass ? 1 : 0;
+        if (glass) H.surf[k].bits |= phx::kSurfGlassIn;
         if (p.surf[k].kind == PHX_REFRACT) glass = p.surf[k].medium == PHX_GLASS;
     }
     for (int g = 0; g < 3; ++g) {
@@ -248,7 +263,7 @@ void build_surfaces(phx_ctx c) {
     bool any = false;
     for (int j = 0; j < phx::kNZern; ++j) any |= a[j] != 0.0;
     for (int j = 0; j < phx::kNZernPoly; ++j) H.zern[j] = z[j];
-    H.surf[0].zernike = any ? 1 : 0;
+    if (any) H.surf[0].bits |= phx::kSurfZernike;
     H.zern_inv_r = 1.0 / p.surf[0].r_outer;
 }
 
@@ -386,6 +401,11 @@ phx_status set_device(phx_ctx c) {
 
 phx_status upload_params(phx_ctx c, hipStream_t stream) {
     if (!c->dirty) return PHX_OK;
+    for (int k = 0; k < c->host.n_surf; ++k) {
+        DevSurface& d = c->host.surf[k];
+        d.coat = d.coating >= 0 && d.coating < c->host.n_coat
+                     ? c->host.coat + (size_t)d.coating * c->host.n_s * c->host.n_lam : nullptr;
+    }
     hipError_t e = hipMemcpyAsync(c->dparams, &c->host, sizeof(DevParams), hipMemcpyHostToDevice,
                                   stream);
     if (e != hipSuccess) return hip_fail(c, e, "hipMemcpyAsync(params)");
@@ -522,6 +542,7 @@ phx_status phx_load_prescription(phx_ctx c, const phx_prescription* p) {
     H.z_start = p->z_start;
     H.obsc_z = p->obscuration_z;
     H.obsc_r = p->obscuration_r;
+    H.obsc_s = sqrt_threshold(p->obscuration_r);
     for (int i = 0; i < 3; ++i) {
         H.sell_b[i] = p->sellmeier_b[i];
         H.sell_c[i] = p->sellmeier_c[i];
@@ -531,7 +552,9 @@ phx_status phx_load_prescription(phx_ctx c, const phx_prescription* p) {
     H.chip_x0 = p->chip_x0;
     H.chip_y0 = p->chip_y0;
     H.pixel = p->pixel;
+    H.inv_pixel = 1.0 / p->pixel;
     H.t_si = p->si_thickness;
+    H.inv_t_si = 1.0 / p->si_thickness;
     H.sigma_max = p->sigma_max;
     // Rajkanan temperature-dependent constants (section 2.4.2)
     const double T = p->si_temperature, kB = 8.617333262e-5;
@@ -543,6 +566,8 @@ phx_status phx_load_prescription(phx_ctx c, const phx_prescription* p) {
     for (int i = 0; i < 2; ++i) {
         H.absorb[i] = std::exp(ep[i] / (kB * T)) - 1.0;
         H.emit[i] = 1.0 - std::exp(-ep[i] / (kB * T));
+        H.inv_absorb[i] = 1.0 / H.absorb[i];
+        H.inv_emit[i] = 1.0 / H.emit[i];
     }
     build_surfaces(c);
     c->have_presc = true;
@@ -1041,7 +1066,7 @@ void set_cull_radii(phx_ctx c, const phx_trace_args* a, phx::Launch& L) {
     // move the landing point on the primary without a useful bound
     if (a->flags & (PHX_F_DOME | PHX_F_HALO | PHX_F_SPIDER | PHX_F_SECOND_KICK)) return;
     const phx::DevSurface& s0 = c->host.surf[0];
-    if (s0.moved || c->presc.n_surfaces < 2) return;
+    if ((s0.bits & phx::kSurfMoved) || c->presc.n_surfaces < 2) return;
     double D = 1e-6;
     if (a->flags & PHX_F_ATMOSPHERE) {
         if (!c->have_screens || c->grad_max.empty()) return;
@@ -1126,7 +1151,7 @@ phx_status validate_launch(phx_ctx c, const phx_trace_args* a, phx::Launch& L, b
     L.event_stride = a->event_stride;
     L.any_sersic = 0;
     for (int s = a->src_begin; s < a->src_end; ++s) L.any_sersic |= c->src[s].kind == 1;
-    L.any_zernike = c->host.surf[0].zernike;
+    L.any_zernike = (c->host.surf[0].bits & phx::kSurfZernike) != 0;
     set_cull_radii(c, a, L);
     if (a->photon_count > 0) {
         L.uniform_count = a->photon_count;

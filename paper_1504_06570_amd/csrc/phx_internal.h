@@ -13,20 +13,38 @@ constexpr int kSedGuide = 1024;   // guide entries per SED for the wavelength se
 constexpr int kNZernPoly = 15;  // monomials u^a v^b, a + b <= 4
 
 // One surface as the kernels read it.  The element frame maps to the global frame by
-// g = R q + t (R row-major); `moved` = 0 means R = identity and t = (0, 0, z_vertex).
-struct DevSurface {
-    int32_t kind, medium, coating, moved;
-    int32_t asphere, zernike;              // asphere: 0 none, 1 even terms only, 2 general
-    int32_t group;                         // rigid-body perturbation group (0 = fixed)
-    int32_t glass_in;                      // the ray arrives through glass (else vacuum)
+// g = R q + t (R row-major); kSurfMoved unset means R = identity and t = (0, 0, z_vertex).  The first
+// 64 bytes hold what every passage of the optics kernel needs, the next 64 the aspheric
+// coefficients: one scalar load each.
+enum : uint32_t {
+    kSurfMoved = 1u << 0,
+    kSurfMirror = 1u << 1,      // reflects (else it refracts; the detector refracts into silicon)
+    kSurfGlass = 1u << 2,       // the medium behind it is glass
+    kSurfGlassIn = 1u << 3,     // the ray arrives through glass (else vacuum)
+    kSurfEven = 1u << 4,        // even aspheric terms only
+    kSurfGeneral = 1u << 5,     // an odd aspheric term is present
+    kSurfZernike = 1u << 6,
+    kSurfPlane = 1u << 7,       // curvature 0 and no aspheric term
+};
+struct alignas(64) DevSurface {
+    uint32_t bits;
+    int32_t coating;
+    double c, kappa1;      // curvature, 1 + kappa
+    double kc2;            // (1 + kappa) c^2
+    double r_in2, r_out2;  // squared aperture radii
+    double tz;             // t[2]
+    const float* coat;     // transmission table of its coating [n_s][n_lam], or null
+    double alpha[8];       // alpha_3 .. alpha_10
     double R[9];
     double t[3];
-    double c, kappa1;      // curvature, 1 + kappa
-    double alpha[8];       // alpha_3 .. alpha_10
     double r_in, r_out;
-    double r_in2, r_out2;  // squared aperture radii
+    int32_t kind, medium;
+    int32_t group;         // rigid-body perturbation group (0 = fixed)
+    int32_t pad;
     double z_vertex;       // nominal vertex height (the group transform acts about a pivot)
+    double pad2[7];
 };
+static_assert(sizeof(DevSurface) == 320, "two 64-byte blocks of scalar loads, then the rest");
 
 struct DevSource {
     double xi, eta, nz;
@@ -66,7 +84,7 @@ struct DevParams {
     int32_t n_surf, nx, ny, n_layers;
     int32_t n_scales, screen_n, n_coat, n_s;
     int32_t n_lam, sed_k, has_glass, pad;
-    DevSurface surf[PHX_MAX_SURF];
+    alignas(64) DevSurface surf[PHX_MAX_SURF];
     double zern[kNZernPoly];   // Zernike deformation of surface 0 as monomial coefficients
     double zern_inv_r;
     double zern_basis[kNZern][kNZernPoly];  // Noll Z4..Z15 as monomial coefficients
@@ -74,11 +92,13 @@ struct DevParams {
     double group_cs[3][4];     // cos t_x, sin t_x, cos t_y, sin t_y of each group's rotation
     double pupil_r_in, pupil_r_out;
     double z_start, obsc_z, obsc_r;
+    double obsc_s;             // smallest s with sqrt(s) >= obsc_r
     double sell_b[3], sell_c[3];
-    double chip_x0, chip_y0, pixel;
+    double chip_x0, chip_y0, pixel, inv_pixel;
     double t_si, sigma_max;
     // Rajkanan constants at the device temperature (section 2.4.2)
     double eg[2], egd, absorb[2], emit[2];
+    double inv_absorb[2], inv_emit[2], inv_t_si;
     // coatings: uniform grid in s = sin^2(theta) and wavelength
     double inv_s_step, lam0, inv_dlam;
     int32_t cull_order[PHX_MAX_SURF]; // coated surfaces, most selective coating first

@@ -55,31 +55,78 @@ __device__ __forceinline__ double rsq_fast(double x) {
     return fma(y, e, y);
 }
 // sqrt(x) for x >= 0 via the reciprocal square root (0 maps to 0).
-__device__ __forceinline__ double sqrt_fast(double x) { return x > 0.0 ? x * rsq_fast(x) : 0.0; }
+__device__ __forceinline__ double sqrt_fast(double x) {
+    const double r = x * rsq_fast(x);   // every lane: a select, not a branch
+    return x > 0.0 ? r : 0.0;
+}
+// a / b rounded as IEEE division rounds it, for well-scaled operands (a may be 0): the reciprocal
+// refined to about half an ulp, then one correction of the quotient by its exact remainder.  The
+// compiler's own sequence is the same with the operands scaled and the special cases restored.
+// div_by takes the rounded reciprocal of a constant b from the host (the correction of a quotient by
+// a rounded reciprocal is the rounded quotient: Markstein, IBM J. Res. Dev. 34, 1990).
+__device__ __forceinline__ double div_by(double a, double b, double r) {
+    const double q = a * r;
+    return fma(fma(-b, q, a), r, q);
+}
+__device__ __forceinline__ double div_norm(double a, double b) { return div_by(a, b, rcp_fast(b)); }
+// sqrt(x) rounded as the IEEE square root rounds it, for a well-scaled x > 0 (the coupled iteration
+// for the root and half its reciprocal, as the compiler writes it between scalings).
+__device__ __forceinline__ double sqrt_norm(double x) {
+    const double y = __builtin_amdgcn_rsq(x);
+    double g = x * y, h = 0.5 * y;
+    const double r = fma(-h, g, 0.5);
+    g = fma(g, r, g);
+    h = fma(h, r, h);
+    g = fma(fma(-g, g, x), h, g);
+    return fma(fma(-g, g, x), h, g);
+}
+
+// a b + c d with the second product rounded.  The geometry names its fused operations: the compiler's own
+// choice among the products of a sum depends on what else it shares a block with, and copies of one
+// passage in different kernels would round differently.
+__device__ __forceinline__ double dot2(double a, double b, double c, double d) {
+    return fma(a, b, c * d);
+}
+
+// A table in device memory reached through a pointer that was itself loaded: named global, or its
+// loads are flat ones, which also wait for the scalar and LDS counters.
+template <class T>
+using Global = const T __attribute__((address_space(1)))*;
+typedef float Float4 __attribute__((ext_vector_type(4)));
 
 struct Rng {
     uint32_t k0, k1, lo, hi;
     __device__ uint4 block(uint32_t b, uint32_t stream = 0) const {
         return philox(make_uint4(lo, hi, b, stream), k0, k1);
     }
+    // The same inside a loop: the key is opaque there, or the compiler keeps the ten rounds' keys in
+    // registers all through the loop.
+    __device__ uint4 block_in_loop(uint32_t b) const {
+        uint32_t a = k0, c = k1;
+        asm volatile("" : "+v"(c));
+        return philox(make_uint4(lo, hi, b, 0u), a, c);
+    }
 };
 
 __device__ __forceinline__ double sellmeier(const DevParams& P, double lam) {
-    const double l2 = (lam * 1e6) * (lam * 1e6);
+    const double lu = lam * 1e6, l2 = lu * lu;
     double s = 1.0;
 #pragma unroll
-    for (int i = 0; i < 3; ++i) s += P.sell_b[i] * l2 / (l2 - P.sell_c[i]);
+    for (int i = 0; i < 3; ++i) s += div_norm(P.sell_b[i] * l2, fma(lu, lu, -P.sell_c[i]));
     return sqrt(s);
 }
 
+// Photon energy in eV.
+__device__ __forceinline__ double energy_ev(double lam) { return div_norm(kHcEvM, lam); }
+
 __device__ __forceinline__ double n_silicon(double lam) {
-    const double e = kHcEvM / lam;
-    return 3.36 + 0.211 * e + 2.79 * exp((e - 3.30) / 0.398);
+    const double e = energy_ev(lam);
+    return 3.36 + 0.211 * e + 2.79 * exp(div_by(e - 3.30, 0.398, 1.0 / 0.398));
 }
 
 // Rajkanan absorption coefficient in m^-1 (constants at the device temperature precomputed).
 __device__ __forceinline__ double absorption(const DevParams& P, double lam) {
-    const double e = kHcEvM / lam;
+    const double e = energy_ev(lam);
     const double C[2] = {5.5, 4.0};
     const double A[2] = {3.231e2, 7.237e3};
     const double ep[2] = {1.827e-2, 5.773e-2};
@@ -88,15 +135,15 @@ __device__ __forceinline__ double absorption(const DevParams& P, double lam) {
     for (int i = 0; i < 2; ++i) {
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
-            const double a = e - P.eg[j] + ep[i];
-            const double b = e - P.eg[j] - ep[i];
-            double term = 0.0;
-            if (a > 0.0) term += a * a / P.absorb[i];
-            if (b > 0.0) term += b * b / P.emit[i];
+            // (a term below its threshold is zero)
+            const double a = fmax(e - P.eg[j] + ep[i], 0.0);
+            const double b = fmax(e - P.eg[j] - ep[i], 0.0);
+            const double term = div_by(a * a, P.absorb[i], P.inv_absorb[i]) +
+                                div_by(b * b, P.emit[i], P.inv_emit[i]);
             alpha += C[i] * A[j] * term;
         }
     }
-    if (e > P.egd) alpha += 1.052e6 * sqrt(e - P.egd);
+    if (e > P.egd) alpha += 1.052e6 * sqrt_norm(e - P.egd);
     return alpha * 100.0;
 }
 
@@ -123,26 +170,51 @@ __device__ __forceinline__ void zernike_poly(const double* c, double u, double v
     dv = p1 + v * (2.0 * p2 + v * (3.0 * p3 + v * 4.0 * p4));
 }
 
-// Sag S(x, y) and g with (dS/dx, dS/dy) = (x g, y g) + zernike gradient.  Returns false outside
-// the conic's domain.
+// What every passage needs of a surface, read with one scalar load and held in scalar registers.
+// The empty asm keeps the compiler from sinking each field's load to its first use, where the
+// wavefront would wait for it alone: with about ten such waits per surface, 45 % of the optics
+// kernel's wavefront time went into waiting (189 scalar loads per 64 photons; now 93, and 38 %).
+struct SurfRegs {
+    uint32_t bits;
+    int32_t coating;
+    double c, kappa1, kc2, r_in2, r_out2, tz;
+    const float* coat;
+};
+__device__ __forceinline__ SurfRegs surf_regs(const DevSurface& s) {
+    SurfRegs h{s.bits, s.coating, s.c, s.kappa1, s.kc2, s.r_in2, s.r_out2, s.tz, s.coat};
+    asm volatile("" : "+s"(h.bits), "+s"(h.coating), "+s"(h.c), "+s"(h.kappa1), "+s"(h.kc2),
+                      "+s"(h.r_in2), "+s"(h.r_out2), "+s"(h.tz), "+s"(h.coat));
+    return h;
+}
+// Even aspheric coefficients alpha_4, alpha_6, alpha_8, alpha_10.
+struct EvenTerms {
+    double a4, a6, a8, a10;
+};
+__device__ __forceinline__ EvenTerms even_terms(const DevSurface& s) {
+    EvenTerms e{s.alpha[1], s.alpha[3], s.alpha[5], s.alpha[7]};
+    asm volatile("" : "+s"(e.a4), "+s"(e.a6), "+s"(e.a8), "+s"(e.a10));
+    return e;
+}
+
+// Sag S(x, y) and g with (dS/dx, dS/dy) = (x g, y g) + zernike gradient.  Returns the conic's
+// argument: negative outside its domain, where the rest is meaningless.
 template <bool ZERN>
-__device__ __forceinline__ bool sag(const DevParams& P, const DevSurface& s, double x, double y,
-                                    double& S, double& gx, double& gy) {
-    const double r2 = x * x + y * y;
-    const double arg = 1.0 - s.kappa1 * s.c * s.c * r2;
-    if (arg < 0.0) return false;
+__device__ __forceinline__ double sag(const DevParams& P, const DevSurface& s, const SurfRegs& h,
+                                      const EvenTerms& e, double x, double y, double& S,
+                                      double& gx, double& gy) {
+    const double r2 = dot2(x, x, y, y);
+    const double arg = fma(-h.kc2, r2, 1.0);
     // conic: S = c r^2 / (1 + root), dS/dr / r = c / root, root = sqrt(arg); one reciprocal
     // square root and one reciprocal
     const double inv_root = rsq_fast(arg);
     const double root = arg * inv_root;
-    S = s.c * r2 * rcp_fast(1.0 + root);
-    double g = s.c * inv_root;
-    if (s.asphere == 1) {
+    S = h.c * r2 * rcp_fast(1.0 + root);
+    double g = h.c * inv_root;
+    if (h.bits & kSurfEven) {
         // even terms only: Horner in r^2
-        const double* a = s.alpha;
-        S += r2 * r2 * (a[1] + r2 * (a[3] + r2 * (a[5] + r2 * a[7])));
-        g += r2 * (4.0 * a[1] + r2 * (6.0 * a[3] + r2 * (8.0 * a[5] + r2 * 10.0 * a[7])));
-    } else if (s.asphere == 2) {
+        S = fma(r2 * r2, fma(r2, fma(r2, fma(e.a10, r2, e.a8), e.a6), e.a4), S);
+        g = fma(r2, fma(e.a4, 4.0, r2 * fma(e.a6, 6.0, r2 * fma(e.a8, 8.0, r2 * 10.0 * e.a10))), g);
+    } else if (h.bits & kSurfGeneral) {
         // general: sum alpha_i r^i and sum i alpha_i r^(i-2), i = 3..10
         const double r = sqrt_fast(r2);
         double pw = r;          // r^(i-2) for i = 3
@@ -159,63 +231,74 @@ __device__ __forceinline__ bool sag(const DevParams& P, const DevSurface& s, dou
     }
     gx = x * g;
     gy = y * g;
-    if (ZERN && s.zernike) {
+    if (ZERN && (h.bits & kSurfZernike)) {
         double zs, zu, zv;
         zernike_poly(P.zern, x * P.zern_inv_r, y * P.zern_inv_r, zs, zu, zv);
         S += zs;
         gx += zu * P.zern_inv_r;
         gy += zv * P.zern_inv_r;
     }
-    return true;
+    return arg;
 }
 
 // Intersection of the ray q + l d with the surface: exact conic root, then Newton on
 // f(l) = q_z + l d_z - S(q_x + l d_x, q_y + l d_y).  Returns 0 or a status; gx, gy receive the
-// sag gradient at the last evaluation.
-template <bool ZERN>
-__device__ int intersect(const DevParams& P, const DevSurface& s, const double q[3],
-                         const double d[3], double& l, double& gx, double& gy, int& iters) {
-    if (s.c == 0.0 && s.asphere == 0 && !(ZERN && s.zernike)) {
+// sag gradient at the last evaluation.  Lanes whose ray misses run along to the end with
+// meaningless values (the branches are on the surface's kind, the same in every lane): a branch for
+// each way to miss would cut the arithmetic into pieces too short to fill its latencies.  SEARCH (the
+// ghost branch's search): the conic's sums in the other order, as that branch rounds them.
+template <bool ZERN, bool SEARCH = false>
+__device__ __forceinline__ int intersect(const DevParams& P, const DevSurface& s, const SurfRegs& h,
+                                         const double q[3], const double d[3], double& l,
+                                         double& gx, double& gy, int& iters) {
+    const bool zern = ZERN && (h.bits & kSurfZernike);
+    gx = 0.0;
+    gy = 0.0;
+    if ((h.bits & kSurfPlane) && !zern) {
         // a plane (the conic root below with c = 0: l = q_z / -d_z), slope zero
-        if (d[2] == 0.0) return PHX_MISSED;
         l = -q[2] * rcp_fast(d[2]);
-        gx = 0.0;
-        gy = 0.0;
-        return 0;
+        return d[2] == 0.0 ? PHX_MISSED : 0;
     }
-    const double A = s.c * (d[0] * d[0] + d[1] * d[1] + s.kappa1 * d[2] * d[2]);
-    const double B = s.c * (q[0] * d[0] + q[1] * d[1] + s.kappa1 * q[2] * d[2]) - d[2];
-    const double C = s.c * (q[0] * q[0] + q[1] * q[1] + s.kappa1 * q[2] * q[2]) - 2.0 * q[2];
-    const double disc = B * B - A * C;
-    if (disc < 0.0) return PHX_MISSED;
+    const double kq = h.kappa1 * q[2];
+    constexpr int i = SEARCH ? 0 : 1, j = 1 - i;
+    const double A = h.c * fma(d[2], h.kappa1 * d[2], dot2(d[i], d[i], d[j], d[j]));
+    const double B = fma(h.c, fma(d[2], kq, dot2(q[i], d[i], q[j], d[j])), -d[2]);
+    const double C = fma(h.c, fma(q[2], kq, dot2(q[i], q[i], q[j], q[j])), -2.0 * q[2]);
+    const double disc = fma(B, B, -(A * C));
     const double sq = sqrt_fast(disc);
     const double den = B >= 0.0 ? B + sq : B - sq;
-    if (den == 0.0) return PHX_MISSED;
     l = -C * rcp_fast(den);
-    if (s.asphere == 0 && !(ZERN && s.zernike)) {
+    int st = disc < 0.0 || den == 0.0 ? PHX_MISSED : 0;
+    if (!(h.bits & (kSurfEven | kSurfGeneral)) && !zern) {
         // a plain conic: the root is the intersection (a Newton update would be rounding-sized,
         // far below the tolerance); only the slope at the hit point is needed
-        const double x = q[0] + l * d[0], y = q[1] + l * d[1];
-        const double arg = 1.0 - s.kappa1 * s.c * s.c * (x * x + y * y);
-        if (arg < 0.0) return PHX_MISSED;
-        const double g = s.c * rsq_fast(arg);
+        const double x = fma(d[0], l, q[0]), y = fma(d[1], l, q[1]);
+        const double arg = fma(-h.kc2, dot2(x, x, y, y), 1.0);
+        const double g = h.c * rsq_fast(arg);
         gx = x * g;
         gy = y * g;
-        return 0;
+        return arg < 0.0 ? PHX_MISSED : st;
     }
+    const EvenTerms e = even_terms(s);
+    if (st == 0) {
+        st = PHX_NONCONV;
 #pragma unroll 1
-    for (int it = 1; it <= kNewtonMax; ++it) {
-        const double x = q[0] + l * d[0], y = q[1] + l * d[1], z = q[2] + l * d[2];
-        double S;
-        if (!sag<ZERN>(P, s, x, y, S, gx, gy)) return PHX_MISSED;
-        const double fp = d[2] - (gx * d[0] + gy * d[1]);
-        if (fp == 0.0) return PHX_NONCONV;
-        const double dl = (z - S) * rcp_fast(fp);
-        l -= dl;
-        iters += 1;
-        if (fabs(dl) <= kNewtonTol) return 0;
+        for (int it = 1; it <= kNewtonMax; ++it) {
+            const double x = fma(d[0], l, q[0]), y = fma(d[1], l, q[1]);
+            double S;
+            const double arg = sag<ZERN>(P, s, h, e, x, y, S, gx, gy);
+            const double fp = d[2] - dot2(gx, d[0], gy, d[1]);
+            const double dz = fma(d[2], l, q[2]) - S, ifp = rcp_fast(fp), dl = dz * ifp;
+            const bool out = arg < 0.0, flat = fp == 0.0;
+            const bool step = !(out || flat);
+            l = step ? fma(-dz, ifp, l) : l;
+            iters += step;
+            const bool conv = step && fabs(dl) <= kNewtonTol;
+            st = out ? PHX_MISSED : conv ? 0 : PHX_NONCONV;
+            if (!step || conv) break;
+        }
     }
-    return PHX_NONCONV;
+    return st;
 }
 
 // Position of a wavelength on the coating tables' uniform wavelength axis (clamped at the ends):
@@ -231,19 +314,24 @@ __device__ __forceinline__ LamCol lambda_column(const DevParams& P, double lam) 
     return LamCol{il, fl - il};
 }
 
-// Coating transmission (section 2.4.2): bilinear in s = sin^2(incidence) and wavelength.
-__device__ __forceinline__ double coating(const DevParams& P, int c, double s, const LamCol& lc,
-                                          const float* table = nullptr) {
+// Coating transmission (section 2.4.2) from a coating's table: bilinear in s = sin^2(incidence) and
+// wavelength.
+__device__ __forceinline__ double coating(const DevParams& P, const float* table, double s,
+                                          const LamCol& lc) {
     double fs = s * P.inv_s_step;
     fs = fmin(fmax(fs, 0.0), (double)(P.n_s - 1));
     const int is = min((int)floor(fs), P.n_s - 2);
     const double a = fs - is, b = lc.b;
-    const float* r0 = (table ? table : P.coat) + ((size_t)c * P.n_s + is) * P.n_lam + lc.il;
-    const float* r1 = r0 + P.n_lam;
+    Global<float> r0 = (Global<float>)table +
+                       ((uint64_t)(uint32_t)is * (uint32_t)P.n_lam + (uint32_t)lc.il);
+    Global<float> r1 = r0 + P.n_lam;
     return (1.0 - a) * ((1.0 - b) * (double)r0[0] + b * (double)r0[1]) +
            a * ((1.0 - b) * (double)r1[0] + b * (double)r1[1]);
 }
-
+// The reflectance table of the coating whose transmission table is given (ghosts).
+__device__ __forceinline__ const float* reflectance(const DevParams& P, const float* table) {
+    return P.coat_r + (table - P.coat);
+}
 
 // Bilinear interpolation of one gradient screen at screen-pixel coordinates (xs, ys): one
 // 32-byte record per cell holds the four corner gradients.
@@ -253,12 +341,11 @@ __device__ __forceinline__ void screen_tap(const float4* g, int64_t N, double xs
     const double a = xs - fx, b = ys - fy;
     const int64_t m = N - 1;
     const int64_t i0 = (int64_t)fx & m, j0 = (int64_t)fy & m;
-    const float4* rec = g + 2 * (j0 * N + i0);
-    const float4 lo = rec[0], hi = rec[1];   // (i,j) (i+1,j) | (i,j+1) (i+1,j+1)
-    ax = (1.0 - b) * ((1.0 - a) * (double)lo.x + a * (double)lo.z) +
-         b * ((1.0 - a) * (double)hi.x + a * (double)hi.z);
-    ay = (1.0 - b) * ((1.0 - a) * (double)lo.y + a * (double)lo.w) +
-         b * ((1.0 - a) * (double)hi.y + a * (double)hi.w);
+    Global<Float4> rec = (Global<Float4>)g + 2 * (j0 * N + i0);
+    const Float4 lo = rec[0], hi = rec[1];   // (i,j) (i+1,j) | (i,j+1) (i+1,j+1)
+    const double a1 = 1.0 - a, b1 = 1.0 - b;
+    ax = dot2(b1, dot2(a1, (double)lo.x, a, (double)lo.z), b, dot2(a1, (double)hi.x, a, (double)hi.z));
+    ay = dot2(b1, dot2(a1, (double)lo.y, a, (double)lo.w), b, dot2(a1, (double)hi.y, a, (double)hi.w));
 }
 
 __device__ __forceinline__ void normalise(double n[3]) {
@@ -631,9 +718,9 @@ __device__ void photon_front(const DevParams& P, const Launch& L, int si, uint64
         p[1] = r * sphi;
         const DevSurface& s0 = P.surf[0];
         const double r2 = p[0] * p[0] + p[1] * p[1];
-        const double arg = 1.0 - s0.kappa1 * s0.c * s0.c * r2;
-        double z = s0.t[2] + (arg >= 0.0 ? s0.c * r2 / (1.0 + sqrt(arg)) : 0.0);
-        if (s0.asphere) {
+        const double arg = 1.0 - s0.kc2 * r2;
+        double z = s0.tz + (arg >= 0.0 ? s0.c * r2 / (1.0 + sqrt(arg)) : 0.0);
+        if (s0.bits & (kSurfEven | kSurfGeneral)) {
             double pw = r * r2;
             for (int i = 3; i <= 10; ++i) {
                 z += s0.alpha[i - 3] * pw;
@@ -730,7 +817,7 @@ __device__ __forceinline__ int sensor_stage(const DevParams& P, const Launch& L,
                                          double lam, const double* d, double& xc, double& yc) {
     if (L.flags & PHX_F_SILICON) {
         const double alpha = absorption(P, lam);
-        const double L_conv = alpha > 0.0 ? -log(u01(rng.block(1).z)) / alpha : INFINITY;
+        const double L_conv = alpha > 0.0 ? div_norm(-log(u01(rng.block(1).z)), alpha) : INFINITY;
         const double depth = L_conv * fabs(d[2]);
         if (!(depth <= P.t_si)) return PHX_ESCAPED;
         if ((L.flags & PHX_F_DEAD_LAYER) && depth < P.ph.dead) return PHX_DEAD;
@@ -741,8 +828,8 @@ __device__ __forceinline__ int sensor_stage(const DevParams& P, const Launch& L,
             double slope;
             const double sigma = (L.flags & PHX_F_FIELD_DIFFUSION)
                                      ? field_sigma(P, depth, slope)
-                                     : P.sigma_max * (P.t_si - depth) / P.t_si;
-            const double rad = sqrt(-2.0 * log(u01(wd.x)));
+                                     : div_by(P.sigma_max * (P.t_si - depth), P.t_si, P.inv_t_si);
+            const double rad = sqrt_norm(-2.0 * log(u01(wd.x)));
             double sa, ca;
             sincospi(2.0 * u01(wd.y), &sa, &ca);
             xc += sigma * rad * ca;
@@ -759,82 +846,113 @@ struct Hit {
     double dn, l;
 };
 
-// Transform into surface k's frame, intersect, clip to the clear aperture, take the normal and
-// play the coating roulette (sections 2.4.1-2.4.2).  Returns 0 to continue or the photon's fate.
 // Returned by hit_surface when a filter or anti-reflection coating reflects the photon (ghosts).
 constexpr int kGhostReflect = 1000;
 
-// Geometry of a surface passage: transform into surface k's frame, intersect, clip to the clear
-// aperture, take the normal (facing the incoming ray).  Returns 0 or the photon's fate.
-template <bool ZERN, bool TAPE = false>
-__device__ __forceinline__ int hit_geometry(const DevParams& P, int k, const double p[3],
-                                            const double n[3], Hit& h, int& newton) {
-    const DevSurface& s = P.surf[k];
-    if (s.moved) {
+// Into and out of a surface's element frame.
+__device__ __forceinline__ void to_element(const DevSurface& s, const SurfRegs& h, const double p[3],
+                                           const double n[3], double q[3], double d[3]) {
+    if (h.bits & kSurfMoved) {
         const double r0 = p[0] - s.t[0], r1 = p[1] - s.t[1], r2 = p[2] - s.t[2];
 #pragma unroll
         for (int i = 0; i < 3; ++i) {
-            h.q[i] = s.R[i] * r0 + s.R[3 + i] * r1 + s.R[6 + i] * r2;
-            h.d[i] = s.R[i] * n[0] + s.R[3 + i] * n[1] + s.R[6 + i] * n[2];
+            q[i] = fma(s.R[6 + i], r2, dot2(s.R[i], r0, s.R[3 + i], r1));
+            d[i] = fma(s.R[6 + i], n[2], dot2(s.R[i], n[0], s.R[3 + i], n[1]));
         }
     } else {
-        h.q[0] = p[0]; h.q[1] = p[1]; h.q[2] = p[2] - s.t[2];
-        h.d[0] = n[0]; h.d[1] = n[1]; h.d[2] = n[2];
+        q[0] = p[0]; q[1] = p[1]; q[2] = p[2] - h.tz;
+        d[0] = n[0]; d[1] = n[1]; d[2] = n[2];
     }
-    double l, gx = 0.0, gy = 0.0;
-    int st = intersect<ZERN>(P, s, h.q, h.d, l, gx, gy, newton);
-    if (st == 0 && !(l > 0.0)) st = PHX_MISSED;
-    if (st != 0) return st;
-    if (TAPE) h.l = l;
-    h.q[0] += h.d[0] * l; h.q[1] += h.d[1] * l; h.q[2] += h.d[2] * l;
-    const double rq2 = h.q[0] * h.q[0] + h.q[1] * h.q[1];
-    if (rq2 < s.r_in2 || rq2 > s.r_out2) return PHX_VIGNETTED;
-    if (s.c == 0.0 && s.asphere == 0 && !(ZERN && s.zernike)) {
-        h.N[0] = 0.0; h.N[1] = 0.0; h.N[2] = 1.0;   // a plane
+}
+__device__ __forceinline__ void to_global(const DevSurface& s, uint32_t bits, double tz,
+                                          const double q[3], const double d[3], double p[3],
+                                          double n[3]) {
+    if (bits & kSurfMoved) {
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            p[i] = fma(s.R[3 * i + 2], q[2], dot2(s.R[3 * i], q[0], s.R[3 * i + 1], q[1])) + s.t[i];
+            n[i] = fma(s.R[3 * i + 2], d[2], dot2(s.R[3 * i], d[0], s.R[3 * i + 1], d[1]));
+        }
     } else {
-        const double inv = rsq_fast(gx * gx + gy * gy + 1.0);
-        h.N[0] = -gx * inv; h.N[1] = -gy * inv; h.N[2] = inv;
+        p[0] = q[0]; p[1] = q[1]; p[2] = q[2] + tz;
+        n[0] = d[0]; n[1] = d[1]; n[2] = d[2];
     }
-    h.dn = h.d[0] * h.N[0] + h.d[1] * h.N[1] + h.d[2] * h.N[2];
-    if (h.dn > 0.0) { h.N[0] = -h.N[0]; h.N[1] = -h.N[1]; h.N[2] = -h.N[2]; h.dn = -h.dn; }
-    return 0;
 }
 
+__device__ __forceinline__ void advance(Hit& h, double l) {
+#pragma unroll
+    for (int i = 0; i < 3; ++i) h.q[i] = fma(h.d[i], l, h.q[i]);
+}
+// Reflection across the normal (section 2.4.2).
+__device__ __forceinline__ void reflect_ray(Hit& h) {
+#pragma unroll
+    for (int i = 0; i < 3; ++i) h.d[i] = fma(-(2.0 * h.dn), h.N[i], h.d[i]);
+}
+
+// The normal at a hit point from the sag's slope, facing the incoming ray (SEARCH as in intersect).
+template <bool ZERN, bool SEARCH = false>
+__device__ __forceinline__ void hit_normal(uint32_t bits, double gx, double gy, Hit& h) {
+    if ((bits & kSurfPlane) && !(ZERN && (bits & kSurfZernike))) {
+        h.N[0] = 0.0; h.N[1] = 0.0; h.N[2] = 1.0;
+    } else {
+        const double inv = rsq_fast((SEARCH ? dot2(gy, gy, gx, gx) : dot2(gx, gx, gy, gy)) + 1.0);
+        h.N[0] = -gx * inv; h.N[1] = -gy * inv; h.N[2] = inv;
+    }
+    constexpr int i = SEARCH ? 1 : 0, j = 1 - i;
+    h.dn = fma(h.d[2], h.N[2], dot2(h.d[i], h.N[i], h.d[j], h.N[j]));
+    if (h.dn > 0.0) { h.N[0] = -h.N[0]; h.N[1] = -h.N[1]; h.N[2] = -h.N[2]; h.dn = -h.dn; }
+}
+
+// Passage of surface k (the same in every lane): transform into its frame, intersect, clip to the
+// clear aperture, take the normal (facing the incoming ray) and play the coating roulette
+// (sections 2.4.1-2.4.2).  Returns 0 to continue or the photon's fate; a photon that misses keeps
+// the position it came with.
 template <bool ZERN, bool TAPE = false, bool GHOST = false>
 __device__ __forceinline__ int hit_surface(const DevParams& P, const Launch& L, const Rng& rng,
-                                           int k, const double p[3], const double n[3],
-                                           const LamCol& lc, uint4& wc, int& wc_block, Hit& h,
-                                           int& newton) {
-    const int g = hit_geometry<ZERN, TAPE>(P, k, p, n, h, newton);
-    if (g != 0) return g;
+                                           const SurfRegs& sr, int k, const double p[3],
+                                           const double n[3], const LamCol& lc, uint4& wc,
+                                           int& wc_block, Hit& h, int& newton) {
     const DevSurface& s = P.surf[k];
-    if ((L.flags & PHX_F_COATINGS) && s.coating >= 0) {
+    to_element(s, sr, p, n, h.q, h.d);
+    double l, gx, gy;
+    int st = intersect<ZERN>(P, s, sr, h.q, h.d, l, gx, gy, newton);
+    if (st == 0 && !(l > 0.0)) st = PHX_MISSED;
+    if (TAPE) h.l = l;
+    if (st != 0) l = 0.0;
+    advance(h, l);
+    const double rq2 = dot2(h.q[0], h.q[0], h.q[1], h.q[1]);
+    if (st == 0 && (rq2 < sr.r_in2 || rq2 > sr.r_out2)) st = PHX_VIGNETTED;
+    hit_normal<ZERN>(sr.bits, gx, gy, h);
+    if ((L.flags & PHX_F_COATINGS) && sr.coating >= 0) {
         const int blk = 2 + (k >> 2);
-        if (blk != wc_block) { wc = rng.block(blk); wc_block = blk; }
-        const int j = k & 3;
-        const uint32_t w = j == 0 ? wc.x : (j == 1 ? wc.y : (j == 2 ? wc.z : wc.w));
-        const double T = coating(P, s.coating, 1.0 - h.dn * h.dn, lc);
-        if (!(u01(w) < T)) {
-            if (GHOST && (L.flags & PHX_F_GHOSTS) && s.kind != PHX_MIRROR &&
-                u01(w) < T + coating(P, s.coating, 1.0 - h.dn * h.dn, lc, P.coat_r))
-                return kGhostReflect;
-            return PHX_ABSORBED;
+        if (blk != wc_block) { wc = rng.block_in_loop(blk); wc_block = blk; }
+        const uint32_t w = word_of(wc, k & 3);
+        // (a lane that missed reads some entry of the table: the lookup clamps)
+        const double T = coating(P, sr.coat, 1.0 - h.dn * h.dn, lc);
+        const bool lost = !(u01(w) < T);
+        if (GHOST) {
+            if (st == 0 && lost) {
+                st = PHX_ABSORBED;
+                if ((L.flags & PHX_F_GHOSTS) && !(sr.bits & kSurfMirror) &&
+                    u01(w) < T + coating(P, reflectance(P, sr.coat), 1.0 - h.dn * h.dn, lc))
+                    st = kGhostReflect;
+            }
+        } else {
+            st = st == 0 && lost ? PHX_ABSORBED : st;
         }
     }
-    return 0;
+    return st;
 }
 
 // Refraction by the vector form of Snell's law (section 2.4.2); false on total internal
 // reflection.
 __device__ __forceinline__ bool refract(Hit& h, double mu) {
     const double cosi = -h.dn;
-    const double kk = 1.0 - mu * mu * (1.0 - cosi * cosi);
-    if (kk < 0.0) return false;
-    const double f = mu * cosi - sqrt_fast(kk);
-    h.d[0] = mu * h.d[0] + f * h.N[0];
-    h.d[1] = mu * h.d[1] + f * h.N[1];
-    h.d[2] = mu * h.d[2] + f * h.N[2];
-    return true;
+    const double kk = fma(-fma(-cosi, cosi, 1.0), mu * mu, 1.0);
+    const double f = fma(mu, cosi, -sqrt_fast(kk));
+#pragma unroll
+    for (int i = 0; i < 3; ++i) h.d[i] = fma(mu, h.d[i], f * h.N[i]);
+    return !(kk < 0.0);   // (the direction of a totally reflected ray is not used)
 }
 
 // Tape of one surface passage for the adjoint: hit point and incoming direction in the
@@ -846,24 +964,38 @@ __device__ __forceinline__ void tape_put(double* tp, uint64_t ts, int k, const H
     t[6 * ts] = h.l;
 }
 
-// A photon between surfaces, in the global frame: position, direction and the index of the
-// medium it travels in.
+// A photon between surfaces, in the global frame: position and direction.  The medium it travels in
+// is a property of the surface it travels to (kSurfGlassIn), the same for every photon.
 struct Ray {
-    double p[3], n[3], n_cur;
+    double p[3], n[3];
 };
 
-// Per-photon constants of the optics stage: the glass index and the coating tables' wavelength
-// column at the photon's wavelength.
+// Per-photon constants of the optics stage: the glass index and its reciprocal (when the surfaces
+// ahead need them) and the coating tables' wavelength column at the photon's wavelength.
 struct Optics {
-    double lam, n_glass;
+    double lam, n_glass, inv_glass;
     LamCol lc;
 };
-__device__ __forceinline__ Optics optics_of(const DevParams& P, const Launch& L, double lam) {
+__device__ __forceinline__ Optics optics_of(const DevParams& P, const Launch& L, double lam,
+                                            bool glass = true) {
     Optics c;
     c.lam = lam;
-    c.n_glass = P.has_glass ? sellmeier(P, lam) : 1.0;
+    c.n_glass = c.inv_glass = 1.0;
+    if (glass && P.has_glass) {
+        c.n_glass = sellmeier(P, lam);
+        c.inv_glass = div_norm(1.0, c.n_glass);
+    }
     c.lc = (L.flags & PHX_F_COATINGS) && P.n_lam > 1 ? lambda_column(P, lam) : LamCol{0, 0.0};
     return c;
+}
+// Index of the medium in front of a surface, and its ratio to the index behind it (media vacuum and
+// glass: 1, n, 1/n; exact where the quotient is).
+__device__ __forceinline__ double index_before(const Optics& oc, uint32_t bits) {
+    return bits & kSurfGlassIn ? oc.n_glass : 1.0;
+}
+__device__ __forceinline__ double index_ratio(const Optics& oc, uint32_t bits) {
+    if (bits & kSurfGlass) return bits & kSurfGlassIn ? 1.0 : oc.inv_glass;
+    return bits & kSurfGlassIn ? oc.n_glass : 1.0;
 }
 
 __device__ __forceinline__ void outcome_init(Outcome& o, double lam) {
@@ -875,9 +1007,9 @@ __device__ __forceinline__ void outcome_init(Outcome& o, double lam) {
 // Central obscuration (section 2.4.1): true, with the outcome filled, if the ray meets it.
 __device__ __forceinline__ bool obscured(const DevParams& P, const Ray& ray, Outcome& o) {
     if (!(P.obsc_r > 0.0)) return false;
-    const double l = (P.obsc_z - ray.p[2]) / ray.n[2];
-    const double x = ray.p[0] + ray.n[0] * l, y = ray.p[1] + ray.n[1] * l;
-    if (!(sqrt(x * x + y * y) < P.obsc_r)) return false;
+    const double l = div_norm(P.obsc_z - ray.p[2], ray.n[2]);
+    const double x = fma(ray.n[0], l, ray.p[0]), y = fma(ray.n[1], l, ray.p[1]);
+    if (!(dot2(x, x, y, y) < P.obsc_s)) return false;   // sqrt(x^2 + y^2) < obsc_r
     o.status = PHX_OBSCURED;
     o.x = x; o.y = y; o.z = P.obsc_z;
     return true;
@@ -991,39 +1123,24 @@ __device__ __forceinline__ bool trace_surfaces(const DevParams& P, const Launch&
 #pragma unroll 1
     for (int k = k0; k < k1; ++k) {
         const DevSurface& s = P.surf[k];
-        int st = hit_surface<ZERN, TAPE, GHOST>(P, L, rng, k, ray.p, ray.n, oc.lc, wc, wc_block,
+        const SurfRegs sr = surf_regs(s);
+        int st = hit_surface<ZERN, TAPE, GHOST>(P, L, rng, sr, k, ray.p, ray.n, oc.lc, wc, wc_block,
                                                 h, o.newton);
         if (GHOST && st == kGhostReflect) {   // GHOST callers pass gs
-            ghost_stage(gs, h, k, ray.n_cur);
+            ghost_stage(gs, h, k, index_before(oc, sr.bits));
             return false;
         }
-        if (st == 0) {
-            if (TAPE) tape_put(tp, ts, k, h);
-            if (s.kind == PHX_MIRROR) {
-                // reflection across the normal (section 2.4.2)
-                h.d[0] -= 2.0 * h.dn * h.N[0];
-                h.d[1] -= 2.0 * h.dn * h.N[1];
-                h.d[2] -= 2.0 * h.dn * h.N[2];
-            } else {
-                const double n2 = s.medium == PHX_GLASS ? oc.n_glass : 1.0;
-                if (refract(h, ray.n_cur / n2)) ray.n_cur = n2; else st = PHX_TIR;
-            }
+        if (TAPE) tape_put(tp, ts, k, h);
+        if (sr.bits & kSurfMirror) {
+            reflect_ray(h);
+        } else if (!refract(h, index_ratio(oc, sr.bits)) && st == 0) {
+            st = PHX_TIR;
         }
         if (st != 0) {
             o.status = st; o.surface = k; o.x = h.q[0]; o.y = h.q[1]; o.z = h.q[2];
             return false;
         }
-        if (s.moved) {
-#pragma unroll
-            for (int i = 0; i < 3; ++i) {
-                ray.p[i] = s.R[3 * i] * h.q[0] + s.R[3 * i + 1] * h.q[1] + s.R[3 * i + 2] * h.q[2] +
-                           s.t[i];
-                ray.n[i] = s.R[3 * i] * h.d[0] + s.R[3 * i + 1] * h.d[1] + s.R[3 * i + 2] * h.d[2];
-            }
-        } else {
-            ray.p[0] = h.q[0]; ray.p[1] = h.q[1]; ray.p[2] = h.q[2] + s.t[2];
-            ray.n[0] = h.d[0]; ray.n[1] = h.d[1]; ray.n[2] = h.d[2];
-        }
+        to_global(s, sr.bits, sr.tz, h.q, h.d, ray.p, ray.n);
     }
     return true;
 }
@@ -1042,8 +1159,8 @@ __device__ __forceinline__ void land(const DevParams& P, const Launch& L, const 
     }
     o.xe = xc; o.ye = yc;
     // pixel quantisation (section 2.4.3)
-    const double fx = (xc - P.chip_x0) / P.pixel, fy = (yc - P.chip_y0) / P.pixel;
-    const double ix = floor(fx), iy = floor(fy);
+    const double ix = floor(div_by(xc - P.chip_x0, P.pixel, P.inv_pixel));
+    const double iy = floor(div_by(yc - P.chip_y0, P.pixel, P.inv_pixel));
     o.status = PHX_OFF_CHIP;
     if (ix >= 0.0 && ix < (double)P.nx && iy >= 0.0 && iy < (double)P.ny) {
         o.status = PHX_DETECTED;
@@ -1081,21 +1198,9 @@ __device__ __forceinline__ void ghost_begin(const DevParams& P, Hit h, int k, do
     gr.from = k;
     gr.inter = 0;
     // reflect at k and return to the global frame
-    h.d[0] -= 2.0 * h.dn * h.N[0];
-    h.d[1] -= 2.0 * h.dn * h.N[1];
-    h.d[2] -= 2.0 * h.dn * h.N[2];
+    reflect_ray(h);
     const DevSurface& s = P.surf[k];
-    if (s.moved) {
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            gr.p[i] = s.R[3 * i] * h.q[0] + s.R[3 * i + 1] * h.q[1] + s.R[3 * i + 2] * h.q[2] +
-                      s.t[i];
-            gr.n[i] = s.R[3 * i] * h.d[0] + s.R[3 * i + 1] * h.d[1] + s.R[3 * i + 2] * h.d[2];
-        }
-    } else {
-        gr.p[0] = h.q[0]; gr.p[1] = h.q[1]; gr.p[2] = h.q[2] + s.t[2];
-        gr.n[0] = h.d[0]; gr.n[1] = h.d[1]; gr.n[2] = h.d[2];
-    }
+    to_global(s, s.bits, s.tz, h.q, h.d, gr.p, gr.n);
 }
 
 // One interaction of a ghost branch; true when the photon's fate is settled (o filled).
@@ -1114,21 +1219,12 @@ __device__ __forceinline__ bool ghost_step(const DevParams& P, const Launch& L, 
         for (int j = 0; j < P.n_surf; ++j) {
             if (j == gr.from) continue;
             const DevSurface& s = P.surf[j];
+            const SurfRegs sr = surf_regs(s);
             double q[3], d[3];
-            if (s.moved) {
-                const double r0 = gr.p[0] - s.t[0], r1 = gr.p[1] - s.t[1], r2 = gr.p[2] - s.t[2];
-#pragma unroll
-                for (int i = 0; i < 3; ++i) {
-                    q[i] = s.R[i] * r0 + s.R[3 + i] * r1 + s.R[6 + i] * r2;
-                    d[i] = s.R[i] * gr.n[0] + s.R[3 + i] * gr.n[1] + s.R[6 + i] * gr.n[2];
-                }
-            } else {
-                q[0] = gr.p[0]; q[1] = gr.p[1]; q[2] = gr.p[2] - s.t[2];
-                d[0] = gr.n[0]; d[1] = gr.n[1]; d[2] = gr.n[2];
-            }
+            to_element(s, sr, gr.p, gr.n, q, d);
             double l, gx, gy;
             int it = 0;
-            if (intersect<ZERN>(P, s, q, d, l, gx, gy, it) == 0 && l > 1e-9 && l < best) {
+            if (intersect<ZERN, true>(P, s, sr, q, d, l, gx, gy, it) == 0 && l > 1e-9 && l < best) {
                 best = l;
                 bk = j;
                 h.q[0] = q[0]; h.q[1] = q[1]; h.q[2] = q[2];
@@ -1149,29 +1245,22 @@ __device__ __forceinline__ bool ghost_step(const DevParams& P, const Launch& L, 
     // the interaction: the hit point, aperture and normal (as the sequential passage takes
     // them), then the roulette with this interaction's own word
     o.newton += bit;
-    h.q[0] += h.d[0] * best; h.q[1] += h.d[1] * best; h.q[2] += h.d[2] * best;
+    advance(h, best);
     {
-        const double rq2 = h.q[0] * h.q[0] + h.q[1] * h.q[1];
+        const double rq2 = dot2(h.q[0], h.q[0], h.q[1], h.q[1]);
         if (rq2 < s.r_in2 || rq2 > s.r_out2) {
             o.status = PHX_VIGNETTED; o.surface = bk; o.x = h.q[0]; o.y = h.q[1]; o.z = h.q[2];
             return true;
         }
-        if (s.c == 0.0 && s.asphere == 0 && !(ZERN && s.zernike)) {
-            h.N[0] = 0.0; h.N[1] = 0.0; h.N[2] = 1.0;   // a plane
-        } else {
-            const double inv = rsq_fast(bgx * bgx + bgy * bgy + 1.0);
-            h.N[0] = -bgx * inv; h.N[1] = -bgy * inv; h.N[2] = inv;
-        }
-        h.dn = h.d[0] * h.N[0] + h.d[1] * h.N[1] + h.d[2] * h.N[2];
-        if (h.dn > 0.0) { h.N[0] = -h.N[0]; h.N[1] = -h.N[1]; h.N[2] = -h.N[2]; h.dn = -h.dn; }
+        hit_normal<ZERN, true>(s.bits, bgx, bgy, h);
     }
     bool reflect = s.kind == PHX_MIRROR;
     if ((L.flags & PHX_F_COATINGS) && s.coating >= 0) {
         const double u = u01(rng.block((uint32_t)gr.inter, 4).x);
         const double sv = 1.0 - h.dn * h.dn;
-        const double T = coating(P, s.coating, sv, oc.lc);
+        const double T = coating(P, s.coat, sv, oc.lc);
         if (!(u < T)) {
-            const double R = s.kind != PHX_MIRROR ? coating(P, s.coating, sv, oc.lc, P.coat_r) : 0.0;
+            const double R = s.kind != PHX_MIRROR ? coating(P, reflectance(P, s.coat), sv, oc.lc) : 0.0;
             if (!(u < T + R)) {
                 o.status = PHX_ABSORBED; o.surface = bk;
                 o.x = h.q[0]; o.y = h.q[1]; o.z = h.q[2];
@@ -1182,9 +1271,7 @@ __device__ __forceinline__ bool ghost_step(const DevParams& P, const Launch& L, 
     }
     const bool det = s.kind == PHX_DETECTOR;
     if (reflect) {
-        h.d[0] -= 2.0 * h.dn * h.N[0];
-        h.d[1] -= 2.0 * h.dn * h.N[1];
-        h.d[2] -= 2.0 * h.dn * h.N[2];
+        reflect_ray(h);
     } else if (!det || (L.flags & PHX_F_SILICON)) {
         const int after = s.medium, before = medium_before(P, bk);
         const int m2 = gr.medium == after ? before : after;
@@ -1200,17 +1287,7 @@ __device__ __forceinline__ bool ghost_step(const DevParams& P, const Launch& L, 
         land(P, L, rng, oc, h, o);
         return true;
     }
-    if (s.moved) {
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            gr.p[i] = s.R[3 * i] * h.q[0] + s.R[3 * i + 1] * h.q[1] + s.R[3 * i + 2] * h.q[2] +
-                      s.t[i];
-            gr.n[i] = s.R[3 * i] * h.d[0] + s.R[3 * i + 1] * h.d[1] + s.R[3 * i + 2] * h.d[2];
-        }
-    } else {
-        gr.p[0] = h.q[0]; gr.p[1] = h.q[1]; gr.p[2] = h.q[2] + s.t[2];
-        gr.n[0] = h.d[0]; gr.n[1] = h.d[1]; gr.n[2] = h.d[2];
-    }
+    to_global(s, s.bits, s.tz, h.q, h.d, gr.p, gr.n);
     gr.from = bk;
     gr.inter += 1;
     return false;
@@ -1226,14 +1303,16 @@ __device__ __forceinline__ void finish_detector(const DevParams& P, const Launch
                                                 GhostSink* gs = nullptr) {
     const int kdet = P.n_surf - 1;
     Hit h;
-    int st = hit_surface<ZERN, TAPE, GHOST>(P, L, rng, kdet, ray.p, ray.n, oc.lc, wc, wc_block, h,
-                                            o.newton);
+    const SurfRegs sr = surf_regs(P.surf[kdet]);
+    int st = hit_surface<ZERN, TAPE, GHOST>(P, L, rng, sr, kdet, ray.p, ray.n, oc.lc, wc, wc_block,
+                                            h, o.newton);
+    const double n_in = index_before(oc, sr.bits);
     if (GHOST && st == kGhostReflect) {   // GHOST callers pass gs
-        ghost_stage(gs, h, kdet, ray.n_cur);
+        ghost_stage(gs, h, kdet, n_in);
         return;
     }
-    if (TAPE && st == 0) tape_put(tp, ts, kdet, h);
-    if (st == 0 && (L.flags & PHX_F_SILICON) && !refract(h, ray.n_cur / n_silicon(oc.lam)))
+    if (TAPE) tape_put(tp, ts, kdet, h);
+    if (st == 0 && (L.flags & PHX_F_SILICON) && !refract(h, div_norm(n_in, n_silicon(oc.lam))))
         st = PHX_TIR;
     if (st != 0) {
         o.status = st;
@@ -1253,7 +1332,7 @@ __device__ Outcome photon_back(const DevParams& P, const Launch& L, int si, uint
     Outcome o;
     outcome_init(o, f.lam);
     const Rng rng{L.seed, (uint32_t)si, (uint32_t)idx, (uint32_t)(idx >> 32)};
-    Ray ray{{f.p[0], f.p[1], f.p[2]}, {f.n[0], f.n[1], f.n[2]}, 1.0};
+    Ray ray{{f.p[0], f.p[1], f.p[2]}, {f.n[0], f.n[1], f.n[2]}};
     if (!entrance<true>(P, L, rng, ray, o)) return o;
     const Optics oc = optics_of(P, L, f.lam);
     uint4 wc = make_uint4(0, 0, 0, 0);
@@ -1322,18 +1401,10 @@ __device__ __forceinline__ int stat_slot(const Outcome& o) {
     return o.status * PHX_STAT_COLS + min(o.surface + 1, PHX_STAT_COLS - 1);
 }
 
-// Wavefront-aggregated status count: lanes with the same (status, surface) slot add their count
-// with one LDS atomic.  Every lane of the wavefront must call it.
+// Status count: one LDS atomic per photon (the LDS unit adds lanes of one address one after the
+// other, beside the wavefronts' arithmetic; electing a leader per status took a hundred instructions).
 __device__ __forceinline__ void count_stat(uint32_t* s_stats, int slot, bool active) {
-    uint64_t pending = __ballot(active);
-    const int lane = __lane_id();
-    while (pending) {
-        const int leader = __ffsll((unsigned long long)pending) - 1;
-        const int key = __shfl(slot, leader);
-        const uint64_t same = __ballot(active && slot == key);
-        if (lane == leader) atomicAdd(&s_stats[key], (uint32_t)__popcll(same));
-        pending &= ~same;
-    }
+    if (active) atomicAdd(&s_stats[slot], 1u);
 }
 
 // Exact per-source moments of converted photons.  Positions are quantised to 2^-44 m and the
@@ -1945,7 +2016,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 8))) 
     __shared__ MomentCache s_mc;
     __shared__ double s_q[kWaves][7][kQueue];   // p, n (global frame) and wavelength
     __shared__ uint32_t s_qr[kWaves][kQueue];   // position in the survivor list
-    __shared__ int32_t s_qk[kWaves][kQueue];    // Newton steps so far << 1 | travelling in glass
+    __shared__ int32_t s_qk[kWaves][kQueue];    // Newton steps so far
     // GH == 1: each wavefront's staging area of ghost starts (kGhostStage fields x 64 lanes)
     __shared__ double s_gs[GH == 1 ? kWaves * kGhostStage * 64 : 1];
     for (int i = threadIdx.x; i < kWin * kWin; i += blockDim.x) s_win[i] = 0;
@@ -1981,7 +2052,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 8))) 
         GhostRay gr;
         Outcome o;
         outcome_init(o, 0.0);
-        Optics oc{0.0, 1.0, LamCol{0, 0.0}};
+        Optics oc{0.0, 1.0, 1.0, LamCol{0, 0.0}};
         Rng rng{0u, 0u, 0u, 0u};
         uint64_t g = 0, idx = 0;
         int si = 0;
@@ -2040,16 +2111,14 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 8))) 
             if (act) {
                 const int e = qn - take + lane;
                 r = qr[e];
-                const int32_t kq = qk[e];
                 g = begin + (surv ? (uint64_t)surv[r] : (uint64_t)r);
                 decode(L, g, si, idx);
                 const Rng rng{L.seed, (uint32_t)si, (uint32_t)idx, (uint32_t)(idx >> 32)};
                 const double lam = q[6][e];
                 outcome_init(o, lam);
-                o.newton = kq >> 1;
+                o.newton = qk[e];
                 const Optics oc = optics_of(P, L, lam);
-                Ray ray{{q[0][e], q[1][e], q[2][e]}, {q[3][e], q[4][e], q[5][e]},
-                        (kq & 1) ? oc.n_glass : 1.0};
+                Ray ray{{q[0][e], q[1][e], q[2][e]}, {q[3][e], q[4][e], q[5][e]}};
                 uint4 wc = make_uint4(0, 0, 0, 0);
                 int wc_block = -1;
                 GhostSink* gp = GHOST ? &gs : nullptr;
@@ -2075,7 +2144,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 8))) 
         outcome_init(o, 0.0);
         uint64_t g = 0, idx = 0;
         int si = 0;
-        Ray ray{{0.0, 0.0, 0.0}, {0.0, 0.0, 1.0}, 1.0};
+        Ray ray{{0.0, 0.0, 0.0}, {0.0, 0.0, 1.0}};
         GhostSink gs{s_gs + (GH == 1 ? wave * kGhostStage * 64 + lane : 0), -1};
         if (valid) {
             g = begin + (surv ? (uint64_t)surv[r] : r);
@@ -2090,7 +2159,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 8))) 
             ray.n[2] = st[5 * st_stride + r];
             const Rng rng{L.seed, (uint32_t)si, (uint32_t)idx, (uint32_t)(idx >> 32)};
             if (entrance<EXTRA>(P, L, rng, ray, o)) {
-                const Optics oc = optics_of(P, L, lam);
+                const Optics oc = optics_of(P, L, lam, !(P.surf[0].bits & kSurfMirror));
                 uint4 wc = make_uint4(0, 0, 0, 0);
                 int wc_block = -1;
                 alive = trace_surfaces<ZERN, false, GHOST>(P, L, rng, oc, ray, 0, k_first, wc,
@@ -2107,7 +2176,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 8))) 
             q[3][e] = ray.n[0]; q[4][e] = ray.n[1]; q[5][e] = ray.n[2];
             q[6][e] = o.lam;
             qr[e] = (uint32_t)r;
-            qk[e] = (o.newton << 1) | (ray.n_cur != 1.0 ? 1 : 0);
+            qk[e] = o.newton;
         }
         qn += __popcll(am);
         const bool done = valid && !alive && !(GHOST && gs.k >= 0);
@@ -2157,16 +2226,16 @@ __device__ __forceinline__ void sag_hessian(const DevParams& P, const DevSurface
                                             double x, double y, double& Sx, double& Sy,
                                             double& Hxx, double& Hxy, double& Hyy) {
     const double r2 = x * x + y * y;
-    const double arg = fmax(1.0 - s.kappa1 * s.c * s.c * r2, 0.0);
+    const double arg = fmax(1.0 - s.kc2 * r2, 0.0);
     const double root = sqrt(arg);
     const double iroot = root > 0.0 ? 1.0 / root : 0.0;
     double g = s.c * iroot;                                       // dS/dr / r
     double gp = 0.5 * s.c * s.kappa1 * s.c * s.c * iroot * iroot * iroot;   // dg / d(r^2)
-    if (s.asphere == 1) {
+    if (s.bits & kSurfEven) {
         const double* a = s.alpha;
         g += r2 * (4.0 * a[1] + r2 * (6.0 * a[3] + r2 * (8.0 * a[5] + r2 * 10.0 * a[7])));
         gp += 4.0 * a[1] + r2 * (12.0 * a[3] + r2 * (24.0 * a[5] + r2 * 40.0 * a[7]));
-    } else if (s.asphere == 2) {
+    } else if (s.bits & kSurfGeneral) {
         const double r = sqrt(r2);
         const double ir = r > 0.0 ? 1.0 / r : 0.0;
         double pw = r;   // r^(i-2)
@@ -2182,7 +2251,7 @@ __device__ __forceinline__ void sag_hessian(const DevParams& P, const DevSurface
     Hxx = g + 2.0 * x * x * gp;
     Hxy = 2.0 * x * y * gp;
     Hyy = g + 2.0 * y * y * gp;
-    if (ZERN && k == 0 && s.zernike) {
+    if (ZERN && k == 0 && (s.bits & kSurfZernike)) {
         const double ir = P.zern_inv_r;
         const double u = x * ir, v = y * ir;
         double pu[5], pv[5];
@@ -2244,7 +2313,7 @@ __device__ void adjoint_sweep(const DevParams& P, const Launch& L, const Rng& rn
         const double sg = dnr > 0.0 ? -1.0 : 1.0;
         const double N[3] = {sg * Nr[0], sg * Nr[1], sg * Nr[2]};
         const double dn = sg * dnr;
-        const double n_in = s.glass_in ? n_glass : 1.0;
+        const double n_in = (s.bits & kSurfGlassIn) ? n_glass : 1.0;
         // 0: no outgoing direction, 1: reflection, 2: refraction
         int mode;
         double mu = 1.0;
