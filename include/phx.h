@@ -420,12 +420,12 @@ phx_status phx_trace(phx_ctx ctx, const phx_trace_args* args, void* stream);
 phx_status phx_trace_noalloc(phx_ctx ctx, const phx_trace_args* args, void* stream);
 
 /* Launch shape of phx_trace / phx_trace_batched / phx_adjoint.  chunk_log2: photons per chunk =
- * 2^chunk_log2 (16..27; the context keeps survivor lists and 56-byte states for two chunks);
+ * 2^chunk_log2 (16..27; the context keeps lists and 48-byte states for two chunks);
  * *_blocks_per_cu: workgroups of 256 lanes per compute unit for the pre-roll, sky+atmosphere and
  * optics kernels (1..64); dynamic_tiles: 0 = static grid-stride, 1 = the sky kernel claims tiles of
  * 2048 photons and each optics wavefront units of 64 from device counters; pipeline: 1 = each
- * chunk's pre-roll bitmap and optics stages run on a context-owned second stream, overlapping
- * the survivor compaction and sky stage of the next chunk on the caller's stream (ordered by
+ * chunk's pre-roll and optics stages run on a context-owned second stream, overlapping
+ * the sort and sky stage of the next chunk on the caller's stream (ordered by
  * events; the caller's stream waits for the last optics stage), 0 = everything on the caller's
  * stream.  Graphs captured by phx_trace_batched follow the same setting.
  * Defaults: 26, 16, 48, 2, 0, 1 (the shape the autotuner settles on for one star of 1e9 photons). */
@@ -519,9 +519,9 @@ phx_status phx_read_image(phx_ctx ctx, const uint32_t* image_dev, uint32_t* imag
 /* Kernel timing for profiling.  While on, phx_trace brackets each kernel it launches with HIP
  * events on the trace stream; phx_get_timing waits for them and returns the accumulated
  * milliseconds per kernel kind since timing was switched on:
- *   out[0] pre-roll bitmap (generate)   out[1] sky + atmosphere (front)
+ *   out[0] pre-roll (generate)          out[1] sky + atmosphere (front)
  *   out[2] optics + silicon (back)      out[3] number of chunks launched
- *   out[4] pre-roll survivor compaction (ordered or by time bucket).
+ *   out[4] sort of the photons to trace.
  * n is the capacity of out (at most 5 values are written).  Switching on resets the totals.
  * Errors: PHX_ERR_INVALID, PHX_ERR_HIP. */
 phx_status phx_set_timing(phx_ctx ctx, int32_t on);

@@ -91,10 +91,10 @@ struct phx_ctx_s {
     double* d_colsum = nullptr;
     double* d_seed = nullptr;            // cotangent coefficients of phx_adjoint_moments
     uint64_t seed_cap = 0;
-    uint64_t* d_bits = nullptr;
-    unsigned int* d_bsum = nullptr;
-    uint8_t* d_key = nullptr;
-    unsigned int* d_hist = nullptr;
+    uint32_t* d_seg = nullptr;           // sort workspace (phx::Workspace)
+    uint32_t* d_seg_n = nullptr;
+    uint32_t* d_hist = nullptr;
+    uint32_t* d_sect = nullptr;
     std::vector<phx::ChunkSpan> plan;   // reserved for kNoAllocMaxChunks chunks at creation
     void* scratch = nullptr;            // device address of this GPU's no-allocation workspace
     double sed_lo = 0.0;                    // lowest SED bin edge (m)
@@ -484,10 +484,10 @@ void phx_destroy(phx_ctx c) {
     free_dev(c->d_partial);
     free_dev(c->d_colsum);
     free_dev(c->d_seed);
-    free_dev(c->d_bits);
-    free_dev(c->d_bsum);
-    free_dev(c->d_key);
+    free_dev(c->d_seg);
+    free_dev(c->d_seg_n);
     free_dev(c->d_hist);
+    free_dev(c->d_sect);
     c->graphs_clear();
     if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
     if (c->aux_stream) (void)hipStreamDestroy(c->aux_stream);
@@ -1187,13 +1187,27 @@ uint32_t guide_shift_of(uint64_t total, int n_src) {
     return shift;
 }
 
-// Chunk plan.  With the atmosphere every chunk has its survivors sorted by time (screen
-// locality; a chunk of many sources keeps their order within a time bucket); traces of big
-// sources are cut at source boundaries, traces of many small sources and adjoints evenly (the
-// adjoint's optics kernel is the heavy stage and wants few, full chunks).  Returns the number of
-// chunks; fills c->plan only if that is at most max_chunks.
+// How a chunk's photons to trace are listed (sort_scatter and class_kernel say what the orders are
+// for).  The order pays once a chunk holds more photons than are in flight at a time (2.6e5 lanes of
+// the sky kernel): with the pre-roll's 13 % from 2^21 photons on, without it from 2^20 on.  Below,
+// and in phx_trace_noalloc's small chunks, the launches cost more than they save.  An adjoint's pre-roll
+// survivors are always sorted: the order of its sums then is the same on every run.
+int list_order(const phx_ctx c, const phx_trace_args* a, uint64_t len, bool adjoint, bool noalloc) {
+    if (noalloc) return phx::kListAsIs;
+    const bool atm = (a->flags & PHX_F_ATMOSPHERE) != 0, coat = (a->flags & PHX_F_COATINGS) != 0;
+    if ((a->flags & PHX_F_CULL) && coat)
+        return adjoint || (atm && len >= (1ull << 21)) ? phx::kListSort : phx::kListAsIs;
+    if (adjoint || len < (1ull << 20)) return phx::kListAsIs;
+    if (atm) return phx::kListSort;
+    return coat && c->host.n_cull > 0 ? phx::kListClass : phx::kListAsIs;
+}
+
+// Chunk plan: traces of big sources through the atmosphere are cut at source boundaries, traces of
+// many small sources and adjoints evenly (the adjoint's optics kernel is the heavy stage and wants
+// few, full chunks).  Returns the number of chunks; fills c->plan only if that is at most
+// max_chunks.
 uint64_t make_plan(phx_ctx c, const phx_trace_args* a, const phx::Launch& L, uint64_t chunk,
-                   bool need_image, uint64_t max_chunks) {
+                   bool need_image, uint64_t max_chunks, bool noalloc = false) {
     const bool atm = (a->flags & PHX_F_ATMOSPHERE) != 0;
     const bool per_source = need_image && atm && L.n_src > 1 &&
                             L.total / (uint64_t)L.n_src >= chunk / 8;
@@ -1215,12 +1229,14 @@ uint64_t make_plan(phx_ctx c, const phx_trace_args* a, const phx::Launch& L, uin
             const uint64_t n_s = L.uniform_count ? L.uniform_count
                                                  : c->src[a->src_begin + s].n_photons;
             for (uint64_t o = 0; o < n_s; o += chunk)
-                c->plan.push_back({start + o, std::min(chunk, n_s - o), start, 1, s});
+                c->plan.push_back({start + o, std::min(chunk, n_s - o), start,
+                                   list_order(c, a, std::min(chunk, n_s - o), false, noalloc), s});
             start += n_s;
         }
     } else {
         for (uint64_t b = 0; b < L.total; b += chunk)
-            c->plan.push_back({b, std::min(chunk, L.total - b), 0, atm ? 1 : 0,
+            c->plan.push_back({b, std::min(chunk, L.total - b), 0,
+                               list_order(c, a, std::min(chunk, L.total - b), !need_image, noalloc),
                                L.n_src == 1 ? 0 : -1});
     }
     return n;
@@ -1319,22 +1335,20 @@ phx_status prepare(phx_ctx c, const phx_trace_args* a, hipStream_t st, phx::Laun
         if (e != hipSuccess) return hip_fail(c, e, "hipStreamSynchronize");
         free_dev(c->d_survivors);
         free_dev(c->d_state);
-        free_dev(c->d_bits);
-        free_dev(c->d_bsum);
-        free_dev(c->d_key);
+        free_dev(c->d_seg);
+        free_dev(c->d_seg_n);
         free_dev(c->d_hist);
         c->ws_chunk = 0;
         c->graphs_clear();
         e = hipMalloc((void**)&c->d_survivors, 2 * chunk * sizeof(uint32_t));
-        if (e == hipSuccess) e = hipMalloc((void**)&c->d_state, 2 * 7 * chunk * sizeof(double));
         if (e == hipSuccess)
-            e = hipMalloc((void**)&c->d_bits, 2 * ((chunk + 63) / 64) * sizeof(uint64_t));
+            e = hipMalloc((void**)&c->d_state, 2 * phx::kStateFields * chunk * sizeof(double));
+        if (e == hipSuccess) e = hipMalloc((void**)&c->d_seg, 2 * chunk * sizeof(uint32_t));
         if (e == hipSuccess)
-            e = hipMalloc((void**)&c->d_bsum, phx::compact_groups(chunk) * sizeof(unsigned int));
-        if (e == hipSuccess) e = hipMalloc((void**)&c->d_key, 2 * chunk);
+            e = hipMalloc((void**)&c->d_seg_n, 2 * phx::max_ranges(chunk) * sizeof(uint32_t));
         if (e == hipSuccess)
-            e = hipMalloc((void**)&c->d_hist, (2 * phx::bucket_groups(chunk) + 1) *
-                                                  phx::kTimeBucketsMax * sizeof(unsigned int));
+            e = hipMalloc((void**)&c->d_hist,
+                          (phx::kSortGroups + 1) * phx::kSortKeys * sizeof(uint32_t));
         if (e != hipSuccess) return fail(c, PHX_ERR_NOMEM, "trace workspace: %s",
                                          hipGetErrorString(e));
         c->ws_chunk = chunk;
@@ -1346,17 +1360,18 @@ phx_status prepare(phx_ctx c, const phx_trace_args* a, hipStream_t st, phx::Laun
         if (e != hipSuccess) return hip_fail(c, e, "hipStreamSynchronize");
         free_dev(c->d_counts);
         free_dev(c->d_tiles);
+        free_dev(c->d_sect);
         c->counts_cap = 0;
         c->graphs_clear();
         e = hipMalloc((void**)&c->d_counts, n_chunks * sizeof(unsigned int));
         if (e == hipSuccess) e = hipMalloc((void**)&c->d_tiles, 2 * n_chunks * sizeof(uint64_t));
+        if (e == hipSuccess) e = hipMalloc((void**)&c->d_sect, 16 * n_chunks * sizeof(uint32_t));
         if (e != hipSuccess) return fail(c, PHX_ERR_NOMEM, "chunk counters");
         c->counts_cap = n_chunks;
     }
     W = phx::Workspace{c->d_survivors, c->d_counts, c->counts_cap, c->d_state, chunk,
-                       (unsigned long long*)c->d_tiles, (unsigned long long*)c->d_bits,
-                       c->d_bsum, c->d_key, c->d_hist, c->plan.data(), (uint64_t)c->plan.size(),
-                       2};
+                       (unsigned long long*)c->d_tiles, c->d_seg, c->d_seg_n, c->d_hist, c->d_sect,
+                       c->plan.data(), (uint64_t)c->plan.size(), 2};
     if (a->flags & PHX_F_GHOSTS) {
         // every traced photon of a chunk may leave one ghost start: a list of chunk entries
         // (14 doubles each; 7.5 GB for chunks of 2^26 photons); grows only
@@ -1448,7 +1463,7 @@ phx_status phx_trace_noalloc(phx_ctx c, const phx_trace_args* a, void* stream) {
     uint64_t chunk = 1024;
     const uint64_t max_chunk = 1ull << std::min(c->chunk_log2, phx::kNoAllocChunkLog2);
     while (chunk < L.total && chunk < max_chunk) chunk <<= 1;
-    const uint64_t n_chunks = make_plan(c, a, L, chunk, true, phx::kNoAllocMaxChunks);
+    const uint64_t n_chunks = make_plan(c, a, L, chunk, true, phx::kNoAllocMaxChunks, true);
     if (n_chunks > phx::kNoAllocMaxChunks)
         return fail(c, PHX_ERR_CAPACITY,
                     "phx_trace_noalloc handles at most %llu chunks of %llu photons, not %llu",
@@ -1473,9 +1488,7 @@ phx_status phx_trace_noalloc(phx_ctx c, const phx_trace_args* a, void* stream) {
     }
     const phx::Workspace W{(uint32_t*)(base + S.survivors), (unsigned int*)(base + S.counts),
                            phx::kNoAllocMaxChunks, (double*)(base + S.state), chunk,
-                           (unsigned long long*)(base + S.tiles),
-                           (unsigned long long*)(base + S.bits), (unsigned int*)(base + S.bsum),
-                           (uint8_t*)(base + S.key), (unsigned int*)(base + S.hist),
+                           (unsigned long long*)(base + S.tiles), nullptr, nullptr, nullptr, nullptr,
                            c->plan.data(), (uint64_t)c->plan.size(), 1};
     r = upload_params(c, st);
     if (r != PHX_OK) return r;
@@ -1498,7 +1511,7 @@ phx_status phx_trace_batched(phx_ctx c, const phx_trace_args* a, void* stream) {
     // fields are appended one by one)
     std::string key((const char*)&L, sizeof(L));
     auto put = [&key](const void* p, size_t n) { key.append((const char*)p, n); };
-    const void* ptrs[] = {W.survivors, W.counts, W.state, W.tiles, W.bits, W.bsum, W.key, W.hist,
+    const void* ptrs[] = {W.survivors, W.counts, W.state, W.tiles, W.seg, W.seg_n, W.hist, W.sect,
                           W.ghost_list, W.ghost_ctr};
     put(ptrs, sizeof(ptrs));
     const uint64_t sizes[] = {W.n_chunks, W.chunk, W.n_plan, (uint64_t)W.buffers, W.ghost_cap};

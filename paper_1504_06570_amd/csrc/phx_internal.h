@@ -159,14 +159,16 @@ struct Launch {
 };
 
 // Scratch of the staged trace: the launch's photon range is processed in chunks; per chunk the
-// pre-roll survivor bitmap, the survivors (offsets within the chunk, in photon order), a
-// survivor counter, and the start-plane state of every traced photon (7 doubles each,
-// structure of arrays).
+// photons to trace (offsets within the chunk), their number, and the start-plane state of every
+// traced photon (kStateFields doubles each, structure of arrays; p_z is the start plane's height).
 constexpr uint64_t kChunk = 1ull << 26;
-// One chunk of a launch: photons [begin, begin + len) of the flattened launch index, and whether
-// its pre-roll survivors are sorted by time bucket.  A chunk inside one source's range names it
-// (src: index relative to the launch's first source, first: the flattened index of that source's
-// first photon); src = -1 for a chunk that spans several sources.
+constexpr int kStateFields = 6;
+// One chunk of a launch: photons [begin, begin + len) of the flattened launch index, and the order
+// in which the photons to trace are listed: as they come, sorted (by pupil sector, by whether they can pass
+// the most selective coating, by time; see sort_scatter), or by that class alone.  A chunk inside one source's range names it (src: index relative to
+// the launch's first source, first: the flattened index of that source's first photon); src = -1
+// for a chunk that spans several sources.
+constexpr int kListAsIs = 0, kListSort = 1, kListClass = 2;
 struct ChunkSpan {
     uint64_t begin, len, first;
     int32_t sort, src;
@@ -175,22 +177,48 @@ struct Workspace {
     uint32_t* survivors;       // [buffers][chunk]
     unsigned int* counts;      // [n_chunks]
     uint64_t n_chunks;
-    double* state;             // [buffers][7][chunk]
+    double* state;             // [buffers][kStateFields][chunk]
     uint64_t chunk;
     unsigned long long* tiles; // [n_chunks][2] tile counters of the dynamic schedule
-    unsigned long long* bits;  // [buffers][chunk / 64] survivor bitmap
-    unsigned int* bsum;        // [compact_groups(chunk)] survivors per compaction workgroup
-    uint8_t* key;              // [buffers][chunk] time bucket of each survivor
-    unsigned int* hist;        // [2 bucket_groups(chunk) + 1][kTimeBucketsMax]: survivors per
-                               // bucket and workgroup, their prefixes over workgroups, totals
+    // sorted chunks only
+    uint32_t* seg;             // [buffers][chunk] listed photons of each range, in photon order
+    uint32_t* seg_n;           // [buffers][max_ranges(chunk)] photons listed per range
+    uint32_t* hist;            // [kSortGroups][kSortKeys] photons per key and sort group, then
+                               // their prefixes over the groups; then [kSortKeys] totals
+    uint32_t* sect;            // [n_chunks][16]: where each pupil sector's photons start, or
+                               // the counter of a list by class
     const ChunkSpan* plan;     // host array: the launch's chunks in order
     uint64_t n_plan;
-    int buffers;               // bitmaps, keys, survivors and states hold this many chunks
-                               // (1 or 2)
+    int buffers;               // lists and states hold this many chunks (1 or 2)
     double* ghost_list = nullptr;          // [kGhostFields][ghost_cap] ghost starts of a chunk
     uint64_t ghost_cap = 0;                 // (with ghosts: at least chunk entries)
     unsigned long long* ghost_ctr = nullptr; // [2] entries listed, entries claimed
 };
+// Photons per pre-roll range (one workgroup's unit): 4096 amortise the range's barriers and keep
+// the two stages' lanes full; a small chunk takes smaller ranges so that they cover the compute
+// units (2e4 photons in 5 ranges of 4096 took 31 us, in 79 of 256 they take 8).
+constexpr int range_log2(uint64_t len) { return len >= (1ull << 22) ? 12 : len >= (1ull << 19) ? 10 : 8; }
+constexpr uint64_t range_count(uint64_t len) {
+    return (len + (1ull << range_log2(len)) - 1) >> range_log2(len);
+}
+constexpr uint64_t max_ranges(uint64_t chunk) {
+    const uint64_t full = (chunk >> 12) + 1;
+    return full > 4096 ? full : 4096;   // 2^22 photons in ranges of 1024
+}
+// The sort's keys and groups of ranges.
+constexpr int kSortKeyBits = 10;         // pupil sector (8) x class (2) x time bucket (64)
+constexpr int kSortKeys = 1 << kSortKeyBits;
+constexpr uint32_t kSortClass = 64;      // the class bit of a key
+constexpr int kSectors = 8;              // one per die
+constexpr uint64_t kSortGroups = 512;    // groups at most
+// log2 of the ranges per group: at least one for each of a group's eight wavefronts.  Groups of
+// 32 ranges left most compute units without one in a chunk of 1e7 photons; more groups than 512 gain
+// nothing alone, and beside the optics stage cost 1e8 photons of 1e4 sources 5.75 -> 6.03 ms.
+constexpr int sort_group_log2(uint64_t n_ranges) {
+    int lg = 3;
+    while (((n_ranges + (1ull << lg) - 1) >> lg) > kSortGroups) ++lg;
+    return lg;
+}
 // Workspace of phx_trace_noalloc: a file-scope device array of kScratchBytes on each GPU (its
 // address is looked up once per device when a context is created), carved into the buffers of
 // one chunk of at most 2^kNoAllocChunkLog2 photons (one buffer set: no pipeline), the per-chunk
@@ -202,21 +230,15 @@ constexpr int kNoAllocMaxSources = 65536;
 constexpr uint64_t kNoAllocGuideMax = 8ull * kNoAllocMaxSources + 2;   // guide blocks + 1
 constexpr uint64_t kScratchBytes = 40ull << 20;
 struct ScratchLayout {
-    uint64_t survivors, state, bits, bsum, key, hist, counts, tiles, prefix, guide, end;
+    uint64_t survivors, state, counts, tiles, prefix, guide, end;
 };
 constexpr uint64_t align256(uint64_t x) { return (x + 255) & ~uint64_t(255); }
 constexpr ScratchLayout scratch_layout() {
     const uint64_t chunk = 1ull << kNoAllocChunkLog2;
-    const uint64_t groups = ((chunk + 63) / 64 + 4095) / 4096;            // compaction
-    const uint64_t bgroups = ((chunk + 63) / 64 + 1023) / 1024;           // time-bucket sort
     ScratchLayout s{};
     s.survivors = 0;
     s.state = align256(s.survivors + chunk * 4);
-    s.bits = align256(s.state + 7 * chunk * 8);
-    s.bsum = align256(s.bits + (chunk + 63) / 64 * 8);
-    s.key = align256(s.bsum + groups * 4);
-    s.hist = align256(s.key + chunk);
-    s.counts = align256(s.hist + (2 * bgroups + 1) * 64 * 4);
+    s.counts = align256(s.state + kStateFields * chunk * 8);
     s.tiles = align256(s.counts + kNoAllocMaxChunks * 4);
     s.prefix = align256(s.tiles + 2 * kNoAllocMaxChunks * 8);
     s.guide = align256(s.prefix + (kNoAllocMaxSources + 1) * 8);
@@ -242,16 +264,6 @@ struct Pipe {
     hipEvent_t* ev = nullptr;    // at least 3 n_chunks + 1 events
     uint64_t n_ev = 0;
 };
-constexpr int kTimeBucketsMax = 64;
-// Workgroups of the ordered compaction for a chunk of n photons (64 photons per bitmap word,
-// 4096 words per workgroup).
-inline uint64_t compact_groups(uint64_t n) { return ((n + 63) / 64 + 4095) / 4096; }
-// Workgroups of the time-bucket sort for a chunk of n photons (1024 bitmap words each).
-constexpr int kBucketWordsPerThread = 4;
-inline uint64_t bucket_groups(uint64_t n) {
-    return ((n + 63) / 64 + kThreads * kBucketWordsPerThread - 1) / (kThreads * kBucketWordsPerThread);
-}
-
 // Launch shape (tunable): workgroups per compute unit of each stage, and the schedule of the
 // sky and optics stages (static grid-stride, or tiles of kTileIters x 256 photons taken from a
 // device counter).
@@ -271,7 +283,7 @@ constexpr uint32_t kBackExtra = PHX_F_AEROSOL | PHX_F_SPIDER | PHX_F_GHOSTS;
 // Optional per-kernel timing: events recorded before/after each kernel launch.
 struct Timing {
     bool on = false;
-    // event pairs per kernel kind (0 generate, 1 front, 2 back, 3 survivor compaction),
+    // event pairs per kernel kind (0 generate, 1 front, 2 back, 3 the sort),
     // appended per chunk
     void (*record)(void* self, int kind, int edge, hipStream_t stream) = nullptr;
     void* self = nullptr;

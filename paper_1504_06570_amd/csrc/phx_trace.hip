@@ -33,8 +33,6 @@ constexpr double kPi = 3.141592653589793;
 constexpr double kNewtonTol = 1e-12;             // m
 constexpr int kNewtonMax = 16;
 constexpr int kBlock = kThreads;
-constexpr int kTimeBuckets = kTimeBucketsMax;   // time buckets of the survivor sort
-static_assert(kTimeBuckets <= 64, "bucket ids are stored in one byte and queued in six bits");
 
 // Reciprocal and reciprocal square root for well-scaled operands (no zeros, infinities or
 // denormals): the hardware estimate refined by two Newton steps, about 1 ulp; used for the
@@ -333,15 +331,18 @@ __device__ __forceinline__ const float* reflectance(const DevParams& P, const fl
     return P.coat_r + (table - P.coat);
 }
 
-// Bilinear interpolation of one gradient screen at screen-pixel coordinates (xs, ys): one
-// 32-byte record per cell holds the four corner gradients.
-__device__ __forceinline__ void screen_tap(const float4* g, int64_t N, double xs, double ys,
+// Bilinear interpolation of one gradient screen at (sx, sy) in metres: one 32-byte record per cell
+// holds the four corner gradients.  The cell index is taken modulo the screen's side (a power of two:
+// every step is exact) in floating point; through 64-bit integers the two conversions take half of
+// the lookup's instructions.
+__device__ __forceinline__ void screen_tap(const float4* g, uint32_t N, double side,
+                                           double inv_side, double sx, double sy, double inv_pix,
                                            double& ax, double& ay) {
-    const double fx = floor(xs), fy = floor(ys);
-    const double a = xs - fx, b = ys - fy;
-    const int64_t m = N - 1;
-    const int64_t i0 = (int64_t)fx & m, j0 = (int64_t)fy & m;
-    Global<Float4> rec = (Global<Float4>)g + 2 * (j0 * N + i0);
+    const double fx = floor(sx * inv_pix), fy = floor(sy * inv_pix);
+    const double a = fma(sx, inv_pix, -fx), b = fma(sy, inv_pix, -fy);
+    const uint32_t i0 = (uint32_t)fma(-side, floor(fx * inv_side), fx);
+    const uint32_t j0 = (uint32_t)fma(-side, floor(fy * inv_side), fy);
+    Global<Float4> rec = (Global<Float4>)g + 2 * (uint64_t)(j0 * N + i0);
     const Float4 lo = rec[0], hi = rec[1];   // (i,j) (i+1,j) | (i,j+1) (i+1,j+1)
     const double a1 = 1.0 - a, b1 = 1.0 - b;
     ax = dot2(b1, dot2(a1, (double)lo.x, a, (double)lo.z), b, dot2(a1, (double)hi.x, a, (double)hi.z));
@@ -404,13 +405,11 @@ __device__ __forceinline__ double wavelength(const DevParams& P, const DevSource
 // Pre-roll test (section 3.2): a photon is culled when a coated surface's roulette draw exceeds
 // the largest transmission that coating has at this wavelength for any angle, so it cannot
 // survive.  The coated surfaces are tested in order of decreasing selectivity.  preroll_draw
-// gives the wavelength (and the time and radius words) from the photon's first Philox blocks.
+// gives the wavelength and block 0 (radius, angle and time words) from the photon's first Philox
+// blocks.
 __device__ __forceinline__ double preroll_draw(const DevParams& P, const Rng& rng,
-                                               const DevSource& src, uint32_t& w_time,
-                                               uint32_t& w_radius) {
-    const uint4 w0 = rng.block(0);
-    w_time = w0.z;
-    w_radius = w0.x;
+                                               const DevSource& src, uint4& w0) {
+    w0 = rng.block(0);
     uint4 w1 = make_uint4(0, 0, 0, 0);
     if (src.sed >= 0) w1 = rng.block(1);
     return wavelength(P, src, w0, w1);
@@ -734,7 +733,8 @@ __device__ void photon_front(const DevParams& P, const Launch& L, int si, uint64
     // deflecting by the wind-shifted screen gradients scaled by (lambda/lambda_ref)^(-1/5)
     if ((L.flags & PHX_F_ATMOSPHERE) && P.n_layers > 0) {
         const double kick = exp(-0.2 * log(lam / P.lambda_ref));
-        const int64_t N = P.screen_n;
+        const uint32_t N = (uint32_t)P.screen_n;
+        const double side = (double)P.screen_n, inv_side = 1.0 / side;
         const bool second = EXTRA && (L.flags & PHX_F_SECOND_KICK);
         uint4 kw0 = make_uint4(0, 0, 0, 0), kw1 = make_uint4(0, 0, 0, 0);
         if (second) {
@@ -753,9 +753,9 @@ __device__ void photon_front(const DevParams& P, const Launch& L, int si, uint64
             double gx = 0.0, gy = 0.0;
 #pragma unroll 1
             for (int s = 0; s < P.n_scales; ++s) {
-                const float4* g = P.grad + ((size_t)(i * P.n_scales + s)) * N * N * 2;
+                const float4* g = P.grad + (size_t)(i * P.n_scales + s) * N * N * 2;
                 double ax, ay;
-                screen_tap(g, N, sx * P.inv_pix[s], sy * P.inv_pix[s], ax, ay);
+                screen_tap(g, N, side, inv_side, sx, sy, P.inv_pix[s], ax, ay);
                 gx += ax;
                 gy += ay;
             }
@@ -1503,20 +1503,24 @@ __device__ __forceinline__ void stats_flush(const Launch& L, uint32_t* s_stats, 
 }
 
 // Pre-roll (section 3.2, dynamic transmission optimisation).  Each workgroup takes contiguous
-// ranges of kGenRange photons.  Stage one draws every photon's wavelength and pupil radius, drops
+// ranges of photons (range_log2).  Stage one draws every photon's wavelength and pupil radius, drops
 // photons whose pupil sample cannot reach the primary's aperture (the annulus is sampled wider
 // than the aperture to leave room for atmospheric displacement, which the host bounds) and
-// applies the most selective coating test; its survivors are queued in LDS (offset, time bucket,
-// wavelength column) and stage two applies the remaining tests to them densely, so the many
+// applies the most selective coating test; its survivors are queued in LDS (offset, wavelength column,
+// sort key) and stage two applies the remaining tests to them densely, so the many
 // photons that fail the first test cost one test.  Stage two also flags the photons whose
 // conversion word passes the escape filter, and stage three (only when any is flagged) runs the
-// exact escape test on them out of the main loops' register budget.  The survivors' bits are set
-// in an LDS copy of the range's bitmap words, written out once (the bitmap does not depend on the
-// order of the queue), with each survivor's time bucket when requested.  An ordered compaction
-// or the time-bucket sort then lists the survivors.
-constexpr int kGenIters = 16;
-constexpr int kGenRange = kBlock * kGenIters;   // photons per range (64 bitmap words)
-static_assert(kGenRange <= 4096, "range offsets are queued in twelve bits");
+// exact escape test on them out of the main loops' register budget.  Last, the survivors' ranks in
+// the range's bitmap (photon order, whatever the queue's) give each its place: in the range's
+// segment, with its sort key, for the sort to list; or straight in the list of photons to trace, behind
+// the ranges that came before (any order of ranges; the images do not depend on it).
+constexpr int kGenRange = 4096;         // photons per range at most (64 bitmap words)
+
+// Sort key of a photon: pupil sector (the top bits of the angle word), class, time bucket (the
+// top bits of the time word: the time stamp is t_e u01(w)).
+__device__ __forceinline__ uint32_t sort_key(const uint4& w0, bool passes) {
+    return ((w0.y >> 29) << 7) | (passes ? kSortClass : 0u) | (w0.z >> 26);
+}
 
 __device__ __forceinline__ void culled_event(const Launch& L, uint64_t g, int si, uint64_t idx,
                                              double lam) {
@@ -1529,21 +1533,36 @@ __device__ __forceinline__ void culled_event(const Launch& L, uint64_t g, int si
     }
 }
 
-// ONE: every photon of the chunk belongs to source one_si, whose first photon has flattened
-// index `first` (the source index and the Philox key are then uniform over the workgroup).
+// Photon r of a chunk: its flattened index, source and index within the source.  ONE: every photon
+// of the chunk belongs to source one_si, whose first photon has flattened index `first` (the source
+// index and the Philox key are then uniform over the workgroup).
+template <bool ONE>
+__device__ __forceinline__ void chunk_photon(const Launch& L, uint64_t begin, uint64_t r, int one_si,
+                                             uint64_t first, uint64_t& g, int& si, uint64_t& idx) {
+    g = begin + r;
+    if constexpr (ONE) {
+        si = one_si;
+        idx = L.photon_begin + (g - first);
+    } else {
+        decode(L, g, si, idx);
+    }
+}
+
 template <bool ONE, bool GHOST>
-__global__ __launch_bounds__(kBlock) void generate_kernel(const DevParams* __restrict__ Pg,
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(6))) void generate_kernel(const DevParams* __restrict__ Pg,
                                                           const Launch L, uint64_t begin,
                                                           uint64_t len, int one_si,
-                                                          uint64_t first,
-                                                          unsigned long long* __restrict__ bits,
-                                                          uint8_t* __restrict__ key) {
-    __shared__ uint32_t s_stats[PHX_STATS_LEN];
+                                                          uint64_t first, int log2_range,
+                                                          uint32_t* __restrict__ seg,
+                                                          uint32_t* __restrict__ seg_n,
+                                                          uint32_t* __restrict__ surv,
+                                                          unsigned int* __restrict__ count) {
     __shared__ unsigned long long s_bits[kGenRange / 64];
-    // queued photon: offset | time bucket << 12 | wavelength column << 18 | escape test << 31
+    __shared__ uint32_t s_pre[kGenRange / 64];   // survivors before each bitmap word
+    // queued photon: offset | wavelength column << 12 | escape test << 31; its sort key
     __shared__ uint32_t s_q[kGenRange];
-    __shared__ unsigned int s_qn, s_esc;
-    stats_init(s_stats);
+    __shared__ uint16_t s_k[kGenRange];
+    __shared__ unsigned int s_qn, s_esc, s_culled, s_base;
     const DevParams& P = *Pg;
     const int lane = __lane_id();
     // with ghosts a photon may leave the sequential path at a coated refracting surface, after
@@ -1554,9 +1573,11 @@ __global__ __launch_bounds__(kBlock) void generate_kernel(const DevParams* __res
     // the chunk's one source, read once (the other case reads each photon's source record)
     DevSource one_src{};
     if constexpr (ONE) one_src = P.src[one_si];
-    const uint64_t n_ranges = (len + kGenRange - 1) / kGenRange;
+    const int n_iter = 1 << (log2_range - 8);
+    const uint64_t n_ranges = (len + (1ull << log2_range) - 1) >> log2_range;
+    if (threadIdx.x == 0) s_culled = 0;
     for (uint64_t rg = blockIdx.x; rg < n_ranges; rg += gridDim.x) {   // workgroup-uniform
-        const uint64_t r0 = rg * kGenRange;
+        const uint64_t r0 = rg << log2_range;
         if (threadIdx.x < kGenRange / 64) s_bits[threadIdx.x] = 0ull;
         if (threadIdx.x == 0) {
             s_qn = 0;
@@ -1564,69 +1585,59 @@ __global__ __launch_bounds__(kBlock) void generate_kernel(const DevParams* __res
         }
         __syncthreads();
         // stage one: wavelength and the first test for every photon of the range
-        for (int it = 0; it < kGenIters; ++it) {
+        for (int it = 0; it < n_iter; ++it) {
             const int rr = it * kBlock + threadIdx.x;
             const uint64_t r = r0 + rr;
             bool pass = false, culled = false;
-            uint32_t entry = 0;
+            uint32_t entry = 0, key = 0;
             if (r < len) {
-                const uint64_t g = begin + r;
+                uint64_t g, idx;
                 int si;
-                uint64_t idx;
-                if constexpr (ONE) {
-                    si = one_si;
-                    idx = L.photon_begin + (g - first);
-                } else {
-                    decode(L, g, si, idx);
-                }
+                chunk_photon<ONE>(L, begin, r, one_si, first, g, si, idx);
                 const Rng rng{L.seed, (uint32_t)si, (uint32_t)idx, (uint32_t)(idx >> 32)};
-                uint32_t wt, wr;
-                const double lam = preroll_draw(P, rng, ONE ? one_src : P.src[si], wt, wr);
+                uint4 w0;
+                const double lam = preroll_draw(P, rng, ONE ? one_src : P.src[si], w0);
                 // squared pupil radius as the sky stage samples it: outside the reachable annulus
                 // the photon is vignetted at the primary whatever the atmosphere does (the bounds
                 // carry a margin far above the rounding of the square root)
                 const double ro = P.pupil_r_out + L.pupil_margin;
                 const double ri = fmax(P.pupil_r_in - L.pupil_margin, 0.0);
-                const double rp2 = u01(wr) * (ro * ro - ri * ri) + ri * ri;
+                const double rp2 = u01(w0.x) * (ro * ro - ri * ri) + ri * ri;
                 const int il = lambda_column(P, lam).il;
                 culled = rp2 < L.cull_r2_lo || rp2 > L.cull_r2_hi ||
                          (n_tests > 0 && preroll_first<GHOST>(P, rng, il, k_lim));
                 pass = !culled;
                 if (culled) culled_event(L, g, si, idx, lam);
-                // time bucket of a survivor (the time stamp is t_e u01(wt))
-                const int tb = min((int)(u01(wt) * kTimeBuckets), kTimeBuckets - 1);
-                entry = (uint32_t)rr | ((uint32_t)tb << 12) | ((uint32_t)il << 18);
+                entry = (uint32_t)rr | ((uint32_t)il << 12);
+                key = sort_key(w0, true);
             }
             const uint64_t pm = __ballot(pass), cm = __ballot(culled);
             unsigned int base = 0;
             if (lane == 0) {
                 if (pm) base = atomicAdd(&s_qn, (unsigned int)__popcll(pm));
-                if (cm) atomicAdd(&s_stats[PHX_CULLED * PHX_STAT_COLS], (uint32_t)__popcll(cm));
+                if (cm) atomicAdd(&s_culled, (unsigned int)__popcll(cm));
             }
             base = __shfl(base, 0);
-            if (pass) s_q[base + __popcll(pm & ((1ull << lane) - 1ull))] = entry;
+            if (pass) {
+                const unsigned int e = base + __popcll(pm & ((1ull << lane) - 1ull));
+                s_q[e] = entry;
+                s_k[e] = (uint16_t)key;
+            }
         }
         __syncthreads();
         // stage two: the remaining tests for the queued photons
         const unsigned int qn = s_qn;
         for (unsigned int q0 = 0; q0 < qn; q0 += kBlock) {
             const unsigned int qi = q0 + threadIdx.x;
-            bool keep = false, culled = false;
+            bool culled = false;
             if (qi < qn) {
                 const uint32_t entry = s_q[qi];
                 const int rr = (int)(entry & 0xfffu);
-                const uint64_t r = r0 + rr;
-                const uint64_t g = begin + r;
+                uint64_t g, idx;
                 int si;
-                uint64_t idx;
-                if constexpr (ONE) {
-                    si = one_si;
-                    idx = L.photon_begin + (g - first);
-                } else {
-                    decode(L, g, si, idx);
-                }
+                chunk_photon<ONE>(L, begin, r0 + rr, one_si, first, g, si, idx);
                 const Rng rng{L.seed, (uint32_t)si, (uint32_t)idx, (uint32_t)(idx >> 32)};
-                const int il = (int)((entry >> 18) & 0x1fffu);
+                const int il = (int)((entry >> 12) & 0x1fffu);
                 culled = preroll_rest<GHOST>(P, rng, il, n_tests, k_lim);
                 const uint32_t et = P.esc_thr && il >= P.esc_col0 ? P.esc_thr[il] : 0u;
                 bool later = false;
@@ -1639,18 +1650,20 @@ __global__ __launch_bounds__(kBlock) void generate_kernel(const DevParams* __res
                         s_esc = 1u;
                     }
                 }
-                keep = !culled && !later;
-                if (keep) {
+                // with ghosts the photons that the most selective coating turns back stay in: a
+                // class of their own
+                if (GHOST && !culled && n_tests > 0 &&
+                    preroll_first<false>(P, rng, il, PHX_MAX_SURF))
+                    s_k[qi] &= (uint16_t)~kSortClass;
+                if (!culled && !later) {
                     atomicOr(&s_bits[rr >> 6], 1ull << (rr & 63));
-                    if (key) key[r] = (uint8_t)((entry >> 12) & 0x3fu);
                 } else if ((L.flags & PHX_F_EVENTS) && (g % L.event_stride) == 0) {
-                    uint32_t wt, wr;
-                    culled_event(L, g, si, idx, preroll_draw(P, rng, ONE ? one_src : P.src[si], wt, wr));
+                    uint4 w0;
+                    culled_event(L, g, si, idx, preroll_draw(P, rng, ONE ? one_src : P.src[si], w0));
                 }
             }
             const uint64_t cm = __ballot(culled);
-            if (lane == 0 && cm)
-                atomicAdd(&s_stats[PHX_CULLED * PHX_STAT_COLS], (uint32_t)__popcll(cm));
+            if (lane == 0 && cm) atomicAdd(&s_culled, (unsigned int)__popcll(cm));
         }
         // stage three: the exact escape test for the photons stage two flagged
         __syncthreads();
@@ -1661,245 +1674,324 @@ __global__ __launch_bounds__(kBlock) void generate_kernel(const DevParams* __res
                 bool culled = false;
                 if (entry >> 31) {
                     const int rr = (int)(entry & 0xfffu);
-                    const uint64_t r = r0 + rr;
-                    const uint64_t g = begin + r;
+                    uint64_t g, idx;
                     int si;
-                    uint64_t idx;
-                    if constexpr (ONE) {
-                        si = one_si;
-                        idx = L.photon_begin + (g - first);
-                    } else {
-                        decode(L, g, si, idx);
-                    }
+                    chunk_photon<ONE>(L, begin, r0 + rr, one_si, first, g, si, idx);
                     const Rng rng{L.seed, (uint32_t)si, (uint32_t)idx, (uint32_t)(idx >> 32)};
-                    uint32_t wt, wr;
-                    const double lam = preroll_draw(P, rng, ONE ? one_src : P.src[si], wt, wr);
+                    uint4 w0;
+                    const double lam = preroll_draw(P, rng, ONE ? one_src : P.src[si], w0);
                     culled = escape_certain(P, lam, rng.block(1).z);
-                    if (!culled) {
+                    if (!culled)
                         atomicOr(&s_bits[rr >> 6], 1ull << (rr & 63));
-                        if (key) key[r] = (uint8_t)((entry >> 12) & 0x3fu);
-                    } else {
+                    else
                         culled_event(L, g, si, idx, lam);
-                    }
                 }
                 const uint64_t cm = __ballot(culled);
-                if (lane == 0 && cm)
-                    atomicAdd(&s_stats[PHX_CULLED * PHX_STAT_COLS], (uint32_t)__popcll(cm));
+                if (lane == 0 && cm) atomicAdd(&s_culled, (unsigned int)__popcll(cm));
+            }
+            __syncthreads();
+        }
+        // places: wavefront 0 scans the bitmap's counts
+        if (threadIdx.x < 64) {
+            const uint32_t n = (uint32_t)__popcll(s_bits[lane]);
+            uint32_t v = n;
+#pragma unroll
+            for (int d = 1; d < 64; d <<= 1) {
+                const uint32_t o = __shfl_up(v, d);
+                if (lane >= d) v += o;
+            }
+            s_pre[lane] = v - n;
+            if (lane == 63) {
+                if (surv)
+                    s_base = atomicAdd(count, v);
+                else
+                    seg_n[rg] = v;
             }
         }
         __syncthreads();
-        if (threadIdx.x < kGenRange / 64 && r0 + (uint64_t)threadIdx.x * 64 < len)
-            bits[(r0 >> 6) + threadIdx.x] = s_bits[threadIdx.x];
-        __syncthreads();
-    }
-    stats_flush(L, s_stats, 0u, 0u);
-}
-
-// Ordered compaction of the survivor bitmap: kCompactWords words per workgroup.
-constexpr int kWordsPerThread = 16;
-constexpr uint64_t kCompactWords = (uint64_t)kBlock * kWordsPerThread;
-
-__device__ __forceinline__ unsigned int block_sum_u32(unsigned int v, unsigned int* s_tmp) {
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m);
-    if (__lane_id() == 0) s_tmp[threadIdx.x / 64] = v;
-    __syncthreads();
-    unsigned int t = 0;
-    for (int w = 0; w < kBlock / 64; ++w) t += s_tmp[w];
-    __syncthreads();
-    return t;
-}
-
-// Survivors per workgroup range of the bitmap.
-__global__ __launch_bounds__(kBlock) void compact_count(const unsigned long long* __restrict__ bits,
-                                                        uint64_t n_words,
-                                                        unsigned int* __restrict__ bsum) {
-    __shared__ unsigned int s_tmp[kBlock / 64];
-    const uint64_t w0 = (uint64_t)blockIdx.x * kCompactWords;
-    unsigned int c = 0;
-    for (int i = 0; i < kWordsPerThread; ++i) {
-        const uint64_t w = w0 + (uint64_t)i * kBlock + threadIdx.x;
-        if (w < n_words) c += __popcll(bits[w]);
-    }
-    const unsigned int t = block_sum_u32(c, s_tmp);
-    if (threadIdx.x == 0) bsum[blockIdx.x] = t;
-}
-
-// Survivor offsets in photon order; the last workgroup stores the total in *count.
-__global__ __launch_bounds__(kBlock) void compact_scatter(const unsigned long long* __restrict__ bits,
-                                                          uint64_t n_words,
-                                                          const unsigned int* __restrict__ bsum,
-                                                          uint32_t* __restrict__ surv,
-                                                          unsigned int* __restrict__ count) {
-    __shared__ unsigned int s_tmp[kBlock / 64];
-    __shared__ unsigned int s_scan[kBlock];
-    // survivors before this workgroup's range
-    unsigned int pre = 0;
-    for (unsigned int b = threadIdx.x; b < blockIdx.x; b += blockDim.x) pre += bsum[b];
-    const unsigned int base = block_sum_u32(pre, s_tmp);
-    // this thread's words: a contiguous run, so that offsets follow photon order
-    const uint64_t w0 = (uint64_t)blockIdx.x * kCompactWords + (uint64_t)threadIdx.x * kWordsPerThread;
-    unsigned long long wv[kWordsPerThread];
-    unsigned int c = 0;
-#pragma unroll
-    for (int i = 0; i < kWordsPerThread; ++i) {
-        wv[i] = w0 + i < n_words ? bits[w0 + i] : 0ull;
-        c += __popcll(wv[i]);
-    }
-    // inclusive scan of the per-thread counts (Hillis-Steele over the workgroup)
-    s_scan[threadIdx.x] = c;
-    __syncthreads();
-    for (int d = 1; d < kBlock; d <<= 1) {
-        const unsigned int v = threadIdx.x >= (unsigned)d ? s_scan[threadIdx.x - d] : 0u;
-        __syncthreads();
-        s_scan[threadIdx.x] += v;
-        __syncthreads();
-    }
-    unsigned int o = base + s_scan[threadIdx.x] - c;
-#pragma unroll
-    for (int i = 0; i < kWordsPerThread; ++i) {
-        unsigned long long m = wv[i];
-        while (m) {
-            const int bit = __ffsll(m) - 1;
-            surv[o++] = (uint32_t)((w0 + i) * 64 + bit);
-            m &= m - 1;
+        for (unsigned int qi = threadIdx.x; qi < qn; qi += kBlock) {
+            const uint32_t rr = s_q[qi] & 0xfffu;
+            const unsigned long long w = s_bits[rr >> 6];
+            if (!((w >> (rr & 63)) & 1ull)) continue;
+            const uint32_t at = s_pre[rr >> 6] + (uint32_t)__popcll(w & ((1ull << (rr & 63)) - 1ull));
+            if (surv)
+                surv[s_base + at] = (uint32_t)r0 + rr;
+            else
+                seg[r0 + at] = rr | ((uint32_t)s_k[qi] << 12);
         }
+        __syncthreads();
     }
-    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == kBlock - 1) *count = base + s_scan[kBlock - 1];
+    if (threadIdx.x == 0 && L.stats && s_culled)
+        atomicAdd(&L.stats[PHX_CULLED * PHX_STAT_COLS], (unsigned long long)s_culled);
 }
 
-// Time-bucketed compaction (with the atmosphere): a stable counting sort of the survivors by
-// time bucket, so that photons traced together see the same wind-shifted stretch of every phase
-// screen and share its cache lines.  Within a bucket survivors keep photon order; the result is
-// the same on every run.  Each workgroup takes kBucketWords bitmap words; a word's 64 bucket
-// bytes are read with four 16-byte loads before its set bits are visited (in photon order).
-constexpr uint64_t kBucketWords = (uint64_t)kBlock * kBucketWordsPerThread;
+// Without the pre-roll every photon is traced: the sort's segments hold them all, classed by whether
+// the most selective coating can let them pass.
+template <bool ONE>
+__global__ __launch_bounds__(kBlock) void list_kernel(const DevParams* __restrict__ Pg,
+                                                      const Launch L, uint64_t begin, uint64_t len,
+                                                      int one_si, uint64_t first, int log2_range,
+                                                      uint32_t* __restrict__ seg,
+                                                      uint32_t* __restrict__ seg_n) {
+    const DevParams& P = *Pg;
+    const uint64_t n = (uint64_t)gridDim.x * kBlock;
+    for (uint64_t r = (uint64_t)blockIdx.x * kBlock + threadIdx.x; r < len; r += n) {
+        uint64_t g, idx;
+        int si;
+        chunk_photon<ONE>(L, begin, r, one_si, first, g, si, idx);
+        const Rng rng{L.seed, (uint32_t)si, (uint32_t)idx, (uint32_t)(idx >> 32)};
+        uint4 w0;
+        const double lam = preroll_draw(P, rng, P.src[si], w0);
+        bool passes = true;
+        if ((L.flags & PHX_F_COATINGS) && P.n_cull > 0)
+            passes = !preroll_first<false>(P, rng, lambda_column(P, lam).il, PHX_MAX_SURF);
+        const uint64_t rr = r & ((1ull << log2_range) - 1);
+        seg[r] = (uint32_t)rr | (sort_key(w0, passes) << 12);
+        if (rr == 0) seg_n[r >> log2_range] = (uint32_t)min((uint64_t)1 << log2_range, len - r);
+    }
+}
 
+// Without the pre-roll and without an atmosphere only the class matters, and photons of a source
+// should stay together (the moments' sums of a wavefront): one pass lists the photons that the most
+// selective coating can let pass from the front and the ones that it stops from the back, in pieces of a
+// range each (1e7 photons 62 us; as a sort of two keys 213 us).  ctr: photons listed so far, from the front
+// in the low half, from the back in the high half.
+constexpr int kClassRange = 4096;
+
+template <bool ONE>
+__global__ __launch_bounds__(kBlock) void class_kernel(const DevParams* __restrict__ Pg,
+                                                       const Launch L, uint64_t begin, uint64_t len,
+                                                       int one_si, uint64_t first,
+                                                       uint32_t* __restrict__ surv,
+                                                       unsigned int* __restrict__ count,
+                                                       unsigned long long* __restrict__ ctr) {
+    __shared__ unsigned long long s_bits[kClassRange / 64];
+    __shared__ uint32_t s_pre[kClassRange / 64];
+    __shared__ unsigned long long s_base;
+    const DevParams& P = *Pg;
+    const int lane = __lane_id(), wave = threadIdx.x >> 6;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *count = (unsigned int)len;
+    for (uint64_t r0 = (uint64_t)blockIdx.x * kClassRange; r0 < len;
+         r0 += (uint64_t)gridDim.x * kClassRange) {   // workgroup-uniform
+        const uint32_t n = (uint32_t)min((uint64_t)kClassRange, len - r0);
+        for (int it = 0; it < kClassRange / kBlock; ++it) {
+            const uint32_t rr = it * kBlock + threadIdx.x;
+            bool passes = false;
+            if (rr < n) {
+                uint64_t g, idx;
+                int si;
+                chunk_photon<ONE>(L, begin, r0 + rr, one_si, first, g, si, idx);
+                const Rng rng{L.seed, (uint32_t)si, (uint32_t)idx, (uint32_t)(idx >> 32)};
+                uint4 w0;
+                const double lam = preroll_draw(P, rng, P.src[si], w0);
+                passes = !preroll_first<false>(P, rng, lambda_column(P, lam).il, PHX_MAX_SURF);
+            }
+            const unsigned long long b = __ballot(passes);
+            if (lane == 0) s_bits[it * (kBlock / 64) + wave] = b;
+        }
+        __syncthreads();
+        if (wave == 0) {
+            const uint32_t c = (uint32_t)__popcll(s_bits[lane]);
+            uint32_t v = c;
+#pragma unroll
+            for (int d = 1; d < 64; d <<= 1) {
+                const uint32_t o = __shfl_up(v, d);
+                if (lane >= d) v += o;
+            }
+            s_pre[lane] = v - c;
+            if (lane == 63) s_base = atomicAdd(ctr, v | ((unsigned long long)(n - v) << 32));
+        }
+        __syncthreads();
+        const uint64_t front = s_base & 0xffffffffull, back = len - 1 - (s_base >> 32);
+        for (uint32_t rr = threadIdx.x; rr < n; rr += kBlock) {
+            const unsigned long long w = s_bits[rr >> 6];
+            const uint32_t at = s_pre[rr >> 6] + (uint32_t)__popcll(w & ((1ull << lane) - 1ull));
+            surv[(w >> lane) & 1ull ? front + at : back - (rr - at)] = (uint32_t)r0 + rr;
+        }
+        __syncthreads();
+    }
+}
+
+// The sort: a stable counting sort of a chunk's photons to trace by (pupil sector, class, time
+// bucket), over groups of 32 ranges.  What it is for:
+//  - time: photons traced together see the same wind-shifted stretch of every phase screen;
+//  - sector: workgroups go to the eight dies in turn and each die has its own L2, so the sky kernel gives
+//    every die the photons of one eighth of the pupil, whose stretch of the screens is an eighth
+//    as wide;
+//  - class: photons that the most selective coating stops share wavefronts, which end there.
+// sort_count: photons per group and key.  sort_scan: their prefixes over the groups, and the
+// totals.  sort_scatter: each photon's place, from an LDS counter per wavefront and key.  STABLE (an
+// adjoint, whose sums take this order): lanes of one key take their places in lane order, so
+// that the list is the same on every run.  Otherwise the order within a key and wavefront is of
+// no effect, and the plain atomic is cheaper beside the optics stage (1e9 photons 41.7 ms, with
+// the ranking 42.4).
+constexpr int kSortBlock = 512;
+constexpr int kSortWaves = kSortBlock / 64;
+constexpr int kSortBatch = 8;
+
+// The active lanes of the wavefront that hold this lane's key.
+__device__ __forceinline__ uint64_t same_key(uint32_t key) {
+    uint64_t m = __ballot(1);
+#pragma unroll
+    for (int b = 0; b < kSortKeyBits; ++b) {
+        const bool on = (key >> b) & 1u;
+        const uint64_t v = __ballot(on);
+        m &= on ? v : ~v;
+    }
+    return m;
+}
+
+// f(entry, range) for the photons of this wavefront's ranges, 64 at a time; kSortBatch loads are in flight
+// together (one at a time, a wavefront waited out the memory's latency for every 64 photons).
 template <class F>
-__device__ __forceinline__ void for_each_survivor(unsigned long long m, const uint8_t* key_word,
-                                                  F f) {
-    if (!m) return;
-    const uint4* kp = reinterpret_cast<const uint4*>(key_word);
-    const uint4 k0 = kp[0], k1 = kp[1], k2 = kp[2], k3 = kp[3];
-    const uint32_t kw[16] = {k0.x, k0.y, k0.z, k0.w, k1.x, k1.y, k1.z, k1.w,
-                             k2.x, k2.y, k2.z, k2.w, k3.x, k3.y, k3.z, k3.w};
+__device__ __forceinline__ void for_each_listed(const uint32_t* seg, const uint32_t* seg_n,
+                                                uint64_t n_ranges, int log2_range, int log2_group, F f) {
+    const int lane = threadIdx.x & 63;
+    const int per_wave = (1 << log2_group) / kSortWaves;
+    const uint64_t rg0 = ((uint64_t)blockIdx.x << log2_group) + (threadIdx.x >> 6) * per_wave;
+    for (int i = 0; i < per_wave; ++i) {
+        const uint64_t rg = rg0 + i;
+        if (rg >= n_ranges) break;
+        const uint32_t n = seg_n[rg];
+        const uint32_t* e = seg + (rg << log2_range);
+        for (uint32_t k0 = 0; k0 < n; k0 += 64 * kSortBatch) {
+            uint32_t v[kSortBatch];
 #pragma unroll
-    for (int j = 0; j < 16; ++j) {
-        uint32_t mj = (uint32_t)(m >> (4 * j)) & 0xfu;
-        while (mj) {
-            const int b = __ffs(mj) - 1;
-            f(4 * j + b, (int)((kw[j] >> (8 * b)) & 0xffu));
-            mj &= mj - 1;
+            for (int j = 0; j < kSortBatch; ++j) {
+                const uint32_t k = k0 + 64 * j + lane;
+                v[j] = e[k < n ? k : n - 1];
+            }
+#pragma unroll
+            for (int j = 0; j < kSortBatch; ++j)
+                if (k0 + 64 * j + lane < n) f(v[j], rg);
         }
     }
 }
 
-__global__ __launch_bounds__(kBlock) void bucket_count(const unsigned long long* __restrict__ bits,
-                                                       const uint8_t* __restrict__ key,
-                                                       uint64_t n_words,
-                                                       unsigned int* __restrict__ hist) {
-    __shared__ unsigned int s_h[kTimeBuckets];
-    if (threadIdx.x < kTimeBuckets) s_h[threadIdx.x] = 0;
+__global__ __launch_bounds__(kSortBlock) void sort_count(const uint32_t* __restrict__ seg,
+                                                         const uint32_t* __restrict__ seg_n,
+                                                         uint64_t n_ranges, int log2_range,
+                                                         int log2_group,
+                                                         uint32_t* __restrict__ hist) {
+    __shared__ uint32_t s_h[kSortKeys];
+    for (int k = threadIdx.x; k < kSortKeys; k += kSortBlock) s_h[k] = 0;
     __syncthreads();
-    const uint64_t w0 = (uint64_t)blockIdx.x * kBucketWords;
-    for (int i = 0; i < kBucketWordsPerThread; ++i) {
-        const uint64_t w = w0 + (uint64_t)i * kBlock + threadIdx.x;
-        if (w >= n_words) continue;
-        for_each_survivor(bits[w], key + w * 64, [&](int, int b) { atomicAdd(&s_h[b], 1u); });
-    }
+    for_each_listed(seg, seg_n, n_ranges, log2_range, log2_group,
+                    [&](uint32_t e, uint64_t) { atomicAdd(&s_h[e >> 12], 1u); });
     __syncthreads();
-    if (threadIdx.x < kTimeBuckets) hist[(uint64_t)blockIdx.x * kTimeBuckets + threadIdx.x] = s_h[threadIdx.x];
+    for (int k = threadIdx.x; k < kSortKeys; k += kSortBlock)
+        hist[(uint64_t)blockIdx.x * kSortKeys + k] = s_h[k];
 }
 
-// Per bucket, the exclusive prefix of its survivors over the sort's workgroups (pre[g][b]) and
-// its total (tot[b]): one workgroup per bucket.
-__global__ __launch_bounds__(kBlock) void bucket_scan(const unsigned int* __restrict__ hist,
-                                                      unsigned int n_groups,
-                                                      unsigned int* __restrict__ pre,
-                                                      unsigned int* __restrict__ tot) {
-    __shared__ unsigned int s_scan[kBlock];
-    const int b = blockIdx.x, t = threadIdx.x;
-    unsigned int carry = 0;
-    for (unsigned int g0 = 0; g0 < n_groups; g0 += kBlock) {
-        const unsigned int g = g0 + t;
-        const unsigned int v = g < n_groups ? hist[(uint64_t)g * kTimeBuckets + b] : 0u;
-        s_scan[t] = v;
-        __syncthreads();
-        for (int d = 1; d < kBlock; d <<= 1) {
-            const unsigned int x = t >= d ? s_scan[t - d] : 0u;
-            __syncthreads();
-            s_scan[t] += x;
-            __syncthreads();
-        }
-        if (g < n_groups) pre[(uint64_t)g * kTimeBuckets + b] = carry + s_scan[t] - v;
-        carry += s_scan[kBlock - 1];
-        __syncthreads();
+// One workgroup per 16 keys; 16 threads share a key's groups.
+__global__ __launch_bounds__(kBlock) void sort_scan(uint32_t* __restrict__ hist, uint32_t n_groups,
+                                                    uint32_t* __restrict__ tot) {
+    __shared__ uint32_t s_sum[16][17];
+    const int key = blockIdx.x * 16 + (threadIdx.x & 15), part = threadIdx.x >> 4;
+    const uint32_t per = (n_groups + 15) / 16;
+    const uint32_t a = min(n_groups, part * per), b = min(n_groups, a + per);
+    uint32_t sum = 0;
+#pragma unroll 8
+    for (uint32_t g = a; g < b; ++g) sum += hist[(uint64_t)g * kSortKeys + key];
+    s_sum[part][threadIdx.x & 15] = sum;
+    __syncthreads();
+    uint32_t run = 0, all = 0;
+    for (int p = 0; p < 16; ++p) {
+        const uint32_t v = s_sum[p][threadIdx.x & 15];
+        if (p < part) run += v;
+        all += v;
     }
-    if (t == 0) tot[b] = carry;
+#pragma unroll 8
+    for (uint32_t g = a; g < b; ++g) {
+        const uint32_t v = hist[(uint64_t)g * kSortKeys + key];
+        hist[(uint64_t)g * kSortKeys + key] = run;
+        run += v;
+    }
+    if (part == 0) tot[key] = all;
 }
 
-// Each workgroup's survivors of bucket b start after the survivors of all earlier buckets and
-// those of bucket b in earlier workgroups; the last workgroup stores the total in *count.
-__global__ __launch_bounds__(kBlock) void bucket_scatter(const unsigned long long* __restrict__ bits,
-                                                         const uint8_t* __restrict__ key,
-                                                         uint64_t n_words,
-                                                         const unsigned int* __restrict__ pre,
-                                                         const unsigned int* __restrict__ tot,
-                                                         uint32_t* __restrict__ surv,
-                                                         unsigned int* __restrict__ count) {
-    // per bucket, per thread: count, then slot (a thread holds at most 4 x 64 survivors)
-    __shared__ uint16_t s_c[kTimeBuckets][kBlock];
-    __shared__ unsigned int s_off[kTimeBuckets];
-    static_assert(kBucketWordsPerThread * 64 < 65536, "per-thread counts fit 16 bits");
-    const int t = threadIdx.x;
-    if (t < kTimeBuckets) {
-        unsigned int base = 0, all = 0;
-        for (int c = 0; c < kTimeBuckets; ++c) {
-            const unsigned int tc = tot[c];
-            if (c < t) base += tc;
-            all += tc;
-        }
-        s_off[t] = base + pre[(uint64_t)blockIdx.x * kTimeBuckets + t];
-        if (blockIdx.x == gridDim.x - 1 && t == 0) *count = all;
+template <bool STABLE>
+__global__ __launch_bounds__(kSortBlock) void sort_scatter(const uint32_t* __restrict__ seg,
+                                                           const uint32_t* __restrict__ seg_n,
+                                                           uint64_t n_ranges, int log2_range,
+                                                           int log2_group,
+                                                           const uint32_t* __restrict__ pre,
+                                                           const uint32_t* __restrict__ tot,
+                                                           uint32_t* __restrict__ surv,
+                                                           unsigned int* __restrict__ count,
+                                                           uint32_t* __restrict__ sect) {
+    __shared__ uint32_t s_at[kSortWaves][kSortKeys];   // per wavefront: count, then next place
+    __shared__ uint32_t s_wsum[kSortWaves];
+    static_assert(kSortKeys == 2 * kSortBlock, "two keys per thread");
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    for (int w = 0; w < kSortWaves; ++w)
+        for (int k = threadIdx.x; k < kSortKeys; k += kSortBlock) s_at[w][k] = 0;
+    // where each key's photons start: a scan of the totals, two keys per thread
+    const uint32_t t0 = tot[2 * threadIdx.x], t1 = tot[2 * threadIdx.x + 1];
+    uint32_t v = t0 + t1;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const uint32_t o = __shfl_up(v, d);
+        if (lane >= d) v += o;
     }
+    if (lane == 63) s_wsum[wave] = v;
     __syncthreads();
-    for (int b = 0; b < kTimeBuckets; ++b) s_c[b][t] = 0;
-    const uint64_t w0 = (uint64_t)blockIdx.x * kBucketWords + (uint64_t)t * kBucketWordsPerThread;
-    for (int i = 0; i < kBucketWordsPerThread; ++i) {
-        if (w0 + i >= n_words) break;
-        for_each_survivor(bits[w0 + i], key + (w0 + i) * 64,
-                          [&](int, int b) { s_c[b][t] += 1; });
-    }
-    __syncthreads();
-    if (t < kTimeBuckets) {   // exclusive scan of bucket t over the threads, in thread order
-        unsigned int run = 0;
-        for (int u = 0; u < kBlock; ++u) {
-            const unsigned int v = s_c[t][u];
-            s_c[t][u] = (uint16_t)run;   // a thread's slot within its workgroup's bucket run
-            run += v;
+    for_each_listed(seg, seg_n, n_ranges, log2_range, log2_group,
+                    [&](uint32_t e, uint64_t) { atomicAdd(&s_at[wave][e >> 12], 1u); });
+    uint32_t start = v - (t0 + t1);
+    for (int w = 0; w < wave; ++w) start += s_wsum[w];
+    if (blockIdx.x == 0) {
+        const int k = 2 * threadIdx.x;
+        if ((k & (kSortKeys / kSectors - 1)) == 0) sect[k / (kSortKeys / kSectors)] = start;
+        if (threadIdx.x == kSortBlock - 1) {
+            sect[kSectors] = start + t0 + t1;
+            *count = start + t0 + t1;
         }
     }
     __syncthreads();
-    // slots within the workgroup's run of a bucket: below 4 x 64 x 256 = 65536
-    const unsigned int* o = s_off;
-    for (int i = 0; i < kBucketWordsPerThread; ++i) {
-        if (w0 + i >= n_words) break;
-        const uint64_t base = (w0 + i) * 64;
-        for_each_survivor(bits[w0 + i], key + base, [&](int bit, int b) {
-            surv[o[b] + s_c[b][t]] = (uint32_t)(base + bit);
-            s_c[b][t] += 1;
-        });
-    }
+    const uint32_t* p = pre + (uint64_t)blockIdx.x * kSortKeys + 2 * threadIdx.x;
+    uint32_t at[2] = {start + p[0], start + t0 + p[1]};
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+        for (int w = 0; w < kSortWaves; ++w) {
+            const uint32_t n = s_at[w][2 * threadIdx.x + j];
+            s_at[w][2 * threadIdx.x + j] = at[j];
+            at[j] += n;
+        }
+    __syncthreads();
+    for_each_listed(seg, seg_n, n_ranges, log2_range, log2_group, [&](uint32_t e, uint64_t rg) {
+        uint32_t at = 0;
+        if constexpr (STABLE) {
+            const uint64_t m = same_key(e >> 12);
+            const int first = __ffsll((unsigned long long)m) - 1;
+            if (first == lane) at = atomicAdd(&s_at[wave][e >> 12], (uint32_t)__popcll(m));
+            at = __shfl(at, first) + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
+        } else {
+            at = atomicAdd(&s_at[wave][e >> 12], 1u);
+        }
+        surv[at] = (uint32_t)(rg << log2_range) + (e & 0xfffu);
+    });
 }
 
-// Block-uniform work distribution over [0, n): static (tile = block, block + grid, ...) or
-// dynamic (tiles of kTileIters x blockDim elements claimed from a device counter).
+// Block-uniform work distribution over [0, n): static (tile = block, block + grid, ...), static within
+// this die's pupil sector (sect: the sectors' starts; workgroup b runs on die b mod 8), or dynamic
+// (tiles of kTileIters x blockDim elements claimed from a device counter).
 struct Tiles {
     unsigned long long* ctr;   // null: static
-    uint64_t tile, sub, n;
+    uint64_t tile, sub, n, base, step;
+    __device__ Tiles(unsigned long long* c, const uint32_t* sect, uint64_t total)
+        : ctr(c), tile(blockIdx.x), sub(0), n(total), base(0), step(gridDim.x) {
+        if (sect) {
+            const uint32_t s = blockIdx.x % kSectors;
+            tile = blockIdx.x / kSectors;
+            step = gridDim.x / kSectors;
+            base = sect[s];
+            n = sect[s + 1] - base;
+        }
+    }
     __device__ bool next(unsigned long long* s_tile) {
         if (!ctr) {
-            if (sub) tile += gridDim.x;
+            if (sub) tile += step;
             sub = 1;
             return tile * blockDim.x < n;
         }
@@ -1915,12 +2007,17 @@ struct Tiles {
         sub += 1;
         return tile * blockDim.x < n;
     }
-    __device__ uint64_t index() const { return tile * blockDim.x + threadIdx.x; }
+    // this lane's element; false where the last tile is short
+    __device__ bool element(uint64_t& r) const {
+        const uint64_t k = tile * blockDim.x + threadIdx.x;
+        r = base + k;
+        return k < n;
+    }
 };
 
-// Front half of the trace for the chunk's photons (the survivor list, or every photon when
-// surv is null): sky sampling and the atmosphere, leaving the start-plane state in SoA arrays
-// st[0..6][i] = p_x, p_y, p_z, n_x, n_y, n_z, lambda.
+// Front half of the trace for the chunk's photons (the list, or every photon when surv is null): sky
+// sampling and the atmosphere, leaving the start-plane state in SoA arrays
+// st[0..5][i] = p_x, p_y, n_x, n_y, n_z, lambda (p_z is the start plane's height).
 template <bool SERSIC, bool EXTRA>
 __global__ __launch_bounds__(kBlock) void front_kernel(const DevParams* __restrict__ Pg,
                                                        const Launch L, uint64_t begin,
@@ -1928,14 +2025,14 @@ __global__ __launch_bounds__(kBlock) void front_kernel(const DevParams* __restri
                                                        const unsigned int* __restrict__ count,
                                                        uint64_t n_all, double* __restrict__ st,
                                                        uint64_t st_stride,
-                                                       unsigned long long* tile_ctr) {
+                                                       unsigned long long* tile_ctr,
+                                                       const uint32_t* __restrict__ sect) {
     __shared__ unsigned long long s_tile;
     const DevParams& P = *Pg;
-    const uint64_t n = surv ? (uint64_t)*count : n_all;
-    Tiles T{tile_ctr, blockIdx.x, 0, n};
+    Tiles T(tile_ctr, sect, surv ? (uint64_t)*count : n_all);
     while (T.next(&s_tile)) {
-        const uint64_t r = T.index();
-        if (r >= n) continue;
+        uint64_t r;
+        if (!T.element(r)) continue;
         const uint64_t g = begin + (surv ? (uint64_t)surv[r] : r);
         int si;
         uint64_t idx;
@@ -1944,11 +2041,10 @@ __global__ __launch_bounds__(kBlock) void front_kernel(const DevParams* __restri
         photon_front<SERSIC, EXTRA>(P, L, si, idx, f);
         st[0 * st_stride + r] = f.p[0];
         st[1 * st_stride + r] = f.p[1];
-        st[2 * st_stride + r] = f.p[2];
-        st[3 * st_stride + r] = f.n[0];
-        st[4 * st_stride + r] = f.n[1];
-        st[5 * st_stride + r] = f.n[2];
-        st[6 * st_stride + r] = f.lam;
+        st[2 * st_stride + r] = f.n[0];
+        st[3 * st_stride + r] = f.n[1];
+        st[4 * st_stride + r] = f.n[2];
+        st[5 * st_stride + r] = f.lam;
     }
 }
 
@@ -2149,14 +2245,14 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 8))) 
         if (valid) {
             g = begin + (surv ? (uint64_t)surv[r] : r);
             decode(L, g, si, idx);
-            const double lam = st[6 * st_stride + r];
+            const double lam = st[5 * st_stride + r];
             outcome_init(o, lam);
             ray.p[0] = st[0 * st_stride + r];
             ray.p[1] = st[1 * st_stride + r];
-            ray.p[2] = st[2 * st_stride + r];
-            ray.n[0] = st[3 * st_stride + r];
-            ray.n[1] = st[4 * st_stride + r];
-            ray.n[2] = st[5 * st_stride + r];
+            ray.p[2] = P.z_start;
+            ray.n[0] = st[2 * st_stride + r];
+            ray.n[1] = st[3 * st_stride + r];
+            ray.n[2] = st[4 * st_stride + r];
             const Rng rng{L.seed, (uint32_t)si, (uint32_t)idx, (uint32_t)(idx >> 32)};
             if (entrance<EXTRA>(P, L, rng, ray, o)) {
                 const Optics oc = optics_of(P, L, lam, !(P.surf[0].bits & kSurfMirror));
@@ -2538,11 +2634,11 @@ __global__ __launch_bounds__(kBlock) void adjoint_kernel(const DevParams* __rest
         Front f;
         f.p[0] = st[0 * st_stride + r];
         f.p[1] = st[1 * st_stride + r];
-        f.p[2] = st[2 * st_stride + r];
-        f.n[0] = st[3 * st_stride + r];
-        f.n[1] = st[4 * st_stride + r];
-        f.n[2] = st[5 * st_stride + r];
-        f.lam = st[6 * st_stride + r];
+        f.p[2] = P.z_start;
+        f.n[0] = st[2 * st_stride + r];
+        f.n[1] = st[3 * st_stride + r];
+        f.n[2] = st[4 * st_stride + r];
+        f.lam = st[5 * st_stride + r];
         const Outcome o = photon_back<ZERN, true>(P, L, si, idx, f, tp, ts);
         const bool conv = o.status <= PHX_OFF_CHIP;
         const bool sampled = JAC && A.jac && (g % A.jac_stride) == 0;
@@ -2671,60 +2767,76 @@ __global__ void gradient_kernel(const float* __restrict__ opd, float4* __restric
 
 }  // namespace
 
-// Pre-roll of one chunk, first half: the survivor bitmap `bits` (and each survivor's time bucket
-// in `key` when the chunk's survivors are sorted by time).
-static void preroll_generate(const DevParams* dparams, const Launch& L, int n_cu,
-                             const LaunchConfig& cfg, const ChunkSpan& sp,
-                             unsigned long long* bits, uint8_t* key, hipStream_t stream) {
-    const uint64_t want = (sp.len + kGenRange - 1) / kGenRange;
-    const uint64_t cap = (uint64_t)n_cu * cfg.generate_per_cu;
-    const dim3 gg((unsigned)(want < cap ? want : cap));
-    const bool ghost = (L.flags & PHX_F_GHOSTS) != 0;
-    if (sp.src >= 0) {
-        const auto gk = ghost ? generate_kernel<true, true> : generate_kernel<true, false>;
-        hipLaunchKernelGGL(gk, gg, dim3(kBlock), 0, stream, dparams, L, sp.begin, sp.len,
-                           L.src_begin + sp.src, sp.first, bits, key);
-    } else {
-        const auto gk = ghost ? generate_kernel<false, true> : generate_kernel<false, false>;
-        hipLaunchKernelGGL(gk, gg, dim3(kBlock), 0, stream, dparams, L, sp.begin, sp.len, 0,
-                           (uint64_t)0, bits, key);
-    }
+// Workgroups for n units of work, at most per_cu per compute unit.
+static dim3 grid_of(uint64_t n, int n_cu, int per_cu) {
+    const uint64_t cap = (uint64_t)n_cu * per_cu;
+    return dim3((unsigned)(n < cap ? n : cap));
 }
 
-// Second half: the survivor list (in photon order, or sorted by time bucket when key is given)
-// and its count.
-static void preroll_compact(const Workspace& W, const ChunkSpan& sp, uint64_t c,
-                            const unsigned long long* bits, const uint8_t* key, uint32_t* surv,
-                            hipStream_t stream) {
-    const uint64_t n_words = (sp.len + 63) / 64;
-    if (key) {
-        const unsigned nbb = (unsigned)((n_words + kBucketWords - 1) / kBucketWords);
-        // hist: [nbb][buckets] counts, then [nbb][buckets] prefixes, then [buckets] totals
-        unsigned int* pre = W.hist + (uint64_t)nbb * kTimeBuckets;
-        unsigned int* tot = pre + (uint64_t)nbb * kTimeBuckets;
-        hipLaunchKernelGGL(bucket_count, dim3(nbb), dim3(kBlock), 0, stream, bits, key, n_words,
-                           W.hist);
-        hipLaunchKernelGGL(bucket_scan, dim3(kTimeBuckets), dim3(kBlock), 0, stream,
-                           (const unsigned int*)W.hist, nbb, pre, tot);
-        hipLaunchKernelGGL(bucket_scatter, dim3(nbb), dim3(kBlock), 0, stream, bits, key, n_words,
-                           (const unsigned int*)pre, (const unsigned int*)tot, surv, W.counts + c);
-        return;
-    }
-    const unsigned nb = (unsigned)((n_words + kCompactWords - 1) / kCompactWords);
-    hipLaunchKernelGGL(compact_count, dim3(nb), dim3(kBlock), 0, stream, bits, n_words, W.bsum);
-    hipLaunchKernelGGL(compact_scatter, dim3(nb), dim3(kBlock), 0, stream, bits, n_words,
-                       (const unsigned int*)W.bsum, surv, W.counts + c);
+// Pre-roll of one chunk: the survivors with their sort keys in the ranges' segments (seg, seg_n), or
+// listed in surv (*count zero before) when the chunk is not sorted.
+static void preroll_generate(const DevParams* dparams, const Launch& L, int n_cu,
+                             const LaunchConfig& cfg, const ChunkSpan& sp, uint32_t* seg,
+                             uint32_t* seg_n, uint32_t* surv, unsigned int* count,
+                             hipStream_t stream) {
+    const dim3 gg = grid_of(range_count(sp.len), n_cu, cfg.generate_per_cu);
+    const bool ghost = (L.flags & PHX_F_GHOSTS) != 0, one = sp.src >= 0;
+    const auto gk = one ? (ghost ? generate_kernel<true, true> : generate_kernel<true, false>)
+                        : (ghost ? generate_kernel<false, true> : generate_kernel<false, false>);
+    hipLaunchKernelGGL(gk, gg, dim3(kBlock), 0, stream, dparams, L, sp.begin, sp.len,
+                       one ? L.src_begin + sp.src : 0, one ? sp.first : (uint64_t)0,
+                       range_log2(sp.len), seg, seg_n, surv, count);
+}
+
+// Every photon of the chunk in the segments (a sorted chunk without the pre-roll).
+static void list_photons(const DevParams* dparams, const Launch& L, int n_cu,
+                         const LaunchConfig& cfg, const ChunkSpan& sp, uint32_t* seg,
+                         uint32_t* seg_n, hipStream_t stream) {
+    const dim3 gg = grid_of((sp.len + kBlock - 1) / kBlock, n_cu, cfg.generate_per_cu);
+    const bool one = sp.src >= 0;
+    hipLaunchKernelGGL(one ? list_kernel<true> : list_kernel<false>, gg, dim3(kBlock), 0, stream,
+                       dparams, L, sp.begin, sp.len, one ? L.src_begin + sp.src : 0,
+                       one ? sp.first : (uint64_t)0, range_log2(sp.len), seg, seg_n);
+}
+
+// Every photon of the chunk listed by class.
+static void class_photons(const DevParams* dparams, const Launch& L, int n_cu,
+                          const LaunchConfig& cfg, const ChunkSpan& sp, uint32_t* surv,
+                          unsigned int* count, unsigned long long* ctr, hipStream_t stream) {
+    const dim3 gg = grid_of((sp.len + kClassRange - 1) / kClassRange, n_cu, cfg.generate_per_cu);
+    const bool one = sp.src >= 0;
+    hipLaunchKernelGGL(one ? class_kernel<true> : class_kernel<false>, gg, dim3(kBlock), 0, stream,
+                       dparams, L, sp.begin, sp.len, one ? L.src_begin + sp.src : 0,
+                       one ? sp.first : (uint64_t)0, surv, count, ctr);
+}
+
+// The segments sorted into surv, their number in W.counts[c], the sectors' starts in W.sect.
+static void sort_photons(const Workspace& W, const ChunkSpan& sp, uint64_t c, const uint32_t* seg,
+                         const uint32_t* seg_n, uint32_t* surv, bool stable,
+                         hipStream_t stream) {
+    const uint64_t n_ranges = range_count(sp.len);
+    const int lr = range_log2(sp.len);
+    const int lg = sort_group_log2(n_ranges);
+    const unsigned groups = (unsigned)((n_ranges + (1u << lg) - 1) >> lg);
+    uint32_t* tot = W.hist + (uint64_t)groups * kSortKeys;
+    hipLaunchKernelGGL(sort_count, dim3(groups), dim3(kSortBlock), 0, stream, seg, seg_n, n_ranges,
+                       lr, lg, W.hist);
+    hipLaunchKernelGGL(sort_scan, dim3(kSortKeys / 16), dim3(kBlock), 0, stream, W.hist, groups, tot);
+    hipLaunchKernelGGL(stable ? sort_scatter<true> : sort_scatter<false>, dim3(groups),
+                       dim3(kSortBlock), 0, stream, seg, seg_n, n_ranges, lr, lg,
+                       (const uint32_t*)W.hist, (const uint32_t*)tot, surv, W.counts + c,
+                       W.sect + 16 * c);
 }
 
 // Chunks are pipelined over two streams when the pipe gives a second one: the arithmetic-bound
-// pre-roll bitmap and optics stage run on pipe.aux, in the order pre-roll(0), pre-roll(1),
-// optics(0), pre-roll(2), optics(1), ..., and the survivor compaction and the bandwidth-bound
+// pre-roll and optics stage run on pipe.aux, in the order pre-roll(0), pre-roll(1),
+// optics(0), pre-roll(2), optics(1), ..., and the sort and the bandwidth-bound
 // sky stage on `stream`, so the two kinds of work share the compute units and neither stream
-// carries much more than the other.  Bitmaps, time keys, survivor lists and states alternate
-// between two buffers; events order the hand-offs (bitmap -> compaction and sky -> optics, and
-// buffer reuse: a chunk's compaction waits for the optics stage two chunks back, and its bitmap
-// is rewritten only by the pre-roll issued after the optics stage that follows the sky stage
-// that read it), the host issues every event record before the waits on it, and the caller's
+// carries much more than the other.  Segments, lists and states alternate
+// between two buffers; events order the hand-offs (segments -> sort and sky -> optics, and
+// buffer reuse: a chunk's sort waits for the optics stage two chunks back, and its segments (or, unsorted,
+// its list) are rewritten only by the pre-roll issued after the optics stage that follows the sky
+// stage that read them), the host issues every event record before the waits on it, and the caller's
 // stream waits for the last optics stage before returning work to it.  Without a second stream
 // each chunk's stages run in order on `stream`.
 namespace {
@@ -2737,6 +2849,7 @@ struct Stages {
     hipStream_t stream;
     const Pipe& pipe;
     const Timing& T;
+    const bool stable;   // the order of the lists has an effect (the adjoint's sums)
     // A launch of one chunk has nothing to overlap: its stages stay on the caller's stream (each
     // hand-off between the streams costs 10-12 us; 1e5 photons through the paraboloid 68 us with
     // them, 27 us without).
@@ -2748,50 +2861,60 @@ struct Stages {
     }
     bool preroll() const { return (L.flags & PHX_F_CULL) && (L.flags & PHX_F_COATINGS); }
     hipStream_t arith() const { return piped() ? pipe.aux : stream; }
-    uint32_t* surv_buf(uint64_t c) const { return W.survivors + (piped() ? c % 2 : 0) * W.chunk; }
-    double* state_buf(uint64_t c) const { return W.state + (piped() ? c % 2 : 0) * 7 * W.chunk; }
-    unsigned long long* bits_buf(uint64_t c) const {
-        return W.bits + (piped() ? c % 2 : 0) * ((W.chunk + 63) / 64);
+    uint64_t half(uint64_t c) const { return piped() ? c % 2 : 0; }
+    uint32_t* surv_buf(uint64_t c) const { return W.survivors + half(c) * W.chunk; }
+    double* state_buf(uint64_t c) const { return W.state + half(c) * kStateFields * W.chunk; }
+    uint32_t* seg_buf(uint64_t c) const { return W.seg + half(c) * W.chunk; }
+    uint32_t* seg_n_buf(uint64_t c) const { return W.seg_n + half(c) * max_ranges(W.chunk); }
+    bool sorted(uint64_t c) const { return W.plan[c].sort == kListSort; }
+    bool classed(uint64_t c) const { return W.plan[c].sort == kListClass; }
+    bool listed(uint64_t c) const { return preroll() || sorted(c) || classed(c); }
+    unsigned long long* class_ctr(uint64_t c) const {
+        return (unsigned long long*)(W.sect + 16 * c);
     }
-    // time keys of chunk c, or null when its survivors keep photon order
-    uint8_t* key_buf(uint64_t c) const {
-        return (W.plan[c].sort && W.key && W.hist) ? W.key + (piped() ? c % 2 : 0) * W.chunk
-                                                   : nullptr;
-    }
-    const uint32_t* surv(uint64_t c) const { return preroll() ? surv_buf(c) : nullptr; }
-    const unsigned int* cnt(uint64_t c) const { return preroll() ? W.counts + c : nullptr; }
+    const uint32_t* surv(uint64_t c) const { return listed(c) ? surv_buf(c) : nullptr; }
+    const unsigned int* cnt(uint64_t c) const { return listed(c) ? W.counts + c : nullptr; }
 
-    // pre-roll bitmap of chunk c
+    // pre-roll of chunk c
     void pre(uint64_t c) const {
         const hipStream_t s = arith();
-        if (preroll()) {
+        if (listed(c)) {
             mark(0, 0, s);
-            preroll_generate(dparams, L, n_cu, cfg, W.plan[c], bits_buf(c), key_buf(c), s);
+            if (preroll())
+                preroll_generate(dparams, L, n_cu, cfg, W.plan[c],
+                                 sorted(c) ? seg_buf(c) : nullptr, sorted(c) ? seg_n_buf(c) : nullptr,
+                                 sorted(c) ? nullptr : surv_buf(c), W.counts + c, s);
+            else if (classed(c))
+                class_photons(dparams, L, n_cu, cfg, W.plan[c], surv_buf(c), W.counts + c,
+                              class_ctr(c), s);
+            else
+                list_photons(dparams, L, n_cu, cfg, W.plan[c], seg_buf(c), seg_n_buf(c), s);
             mark(0, 1, s);
         }
         if (piped()) (void)hipEventRecord(ev(0, c), s);
     }
-    // survivor compaction and sky stage of chunk c on `stream`
+    // sort and sky stage of chunk c on `stream`
     void sky(uint64_t c, unsigned long long* ft) const {
         const ChunkSpan& sp = W.plan[c];
         if (piped()) {
             (void)hipStreamWaitEvent(stream, ev(0, c), 0);
             if (c >= 2) (void)hipStreamWaitEvent(stream, ev(2, c - 2), 0);
         }
-        if (preroll()) {
+        if (sorted(c)) {
             mark(3, 0, stream);
-            preroll_compact(W, sp, c, bits_buf(c), key_buf(c), surv_buf(c), stream);
+            sort_photons(W, sp, c, seg_buf(c), seg_n_buf(c), surv_buf(c), stable, stream);
             mark(3, 1, stream);
         }
-        const uint64_t want = (sp.len + kBlock - 1) / kBlock;
-        const uint64_t fcap = (uint64_t)n_cu * cfg.front_per_cu;
-        const dim3 fg((unsigned)(want < fcap ? want : fcap));
+        const dim3 fg = grid_of((sp.len + kBlock - 1) / kBlock, n_cu, cfg.front_per_cu);
+        // the dies take a pupil sector each (a grid that covers them evenly, the static schedule)
+        const uint32_t* sect = sorted(c) && (L.flags & PHX_F_ATMOSPHERE) && !ft &&
+                                       fg.x % kSectors == 0 ? W.sect + 16 * c : nullptr;
         mark(1, 0, stream);
         const bool extra = (L.flags & kFrontExtra) != 0;
         const auto fk = L.any_sersic ? (extra ? front_kernel<true, true> : front_kernel<true, false>)
                                      : (extra ? front_kernel<false, true> : front_kernel<false, false>);
         hipLaunchKernelGGL(fk, fg, dim3(kBlock), 0, stream, dparams, L, sp.begin, surv(c), cnt(c),
-                           sp.len, state_buf(c), W.chunk, ft);
+                           sp.len, state_buf(c), W.chunk, ft, sect);
         mark(1, 1, stream);
         if (piped()) (void)hipEventRecord(ev(1, c), stream);
     }
@@ -2812,16 +2935,29 @@ struct Stages {
         if (piped() && n_chunks) (void)hipStreamWaitEvent(stream, ev(2, n_chunks - 1), 0);
     }
     bool valid() const {
-        if (!W.state || !W.survivors || !W.counts || !W.bits || !W.bsum) return false;
+        if (!W.state || !W.survivors || !W.counts) return false;
         if ((W.n_plan && !W.plan) || W.n_plan > W.n_chunks) return false;
         if (piped() && (W.buffers < 2 || pipe.n_ev < 3 * W.n_plan + 1)) return false;
         for (uint64_t c = 0; c < W.n_plan; ++c)
-            if (W.plan[c].len > W.chunk) return false;
+            if (W.plan[c].len > W.chunk || (classed(c) && (!W.sect || preroll())) ||
+                (sorted(c) && (!W.seg || !W.seg_n || !W.hist || !W.sect)))
+                return false;
         return true;
     }
     // Issue every chunk's stages; optics(c) is the caller's callback for the optics stage.
     template <class Optics>
     void run(uint64_t n_chunks, bool dynamic, Optics optics) const {
+        bool direct = false, cls = false;   // counters that the kernels add to
+        for (uint64_t c = 0; c < n_chunks; ++c) {
+            direct |= preroll() && !sorted(c);
+            cls |= classed(c);
+        }
+        if (cls)
+            hipLaunchKernelGGL(fill_u32, dim3((unsigned)((16 * n_chunks + 255) / 256)), dim3(256), 0,
+                               stream, W.sect, 16 * n_chunks, 0u);
+        if (direct)
+            hipLaunchKernelGGL(fill_u32, dim3((unsigned)((n_chunks + 255) / 256)), dim3(256), 0,
+                               stream, W.counts, n_chunks, 0u);
         fork(n_chunks);
         if (!piped()) {
             for (uint64_t c = 0; c < n_chunks; ++c) {
@@ -2853,7 +2989,7 @@ hipError_t launch_trace(const DevParams* dparams, const Launch& L, const Workspa
                         const LaunchConfig& cfg, hipStream_t stream, const Pipe& pipe,
                         const Timing& T) {
     if (L.total == 0) return hipSuccess;
-    const Stages S{dparams, L, W, n_cu, cfg, stream, pipe, T};
+    const Stages S{dparams, L, W, n_cu, cfg, stream, pipe, T, false};
     if (!S.valid()) return hipErrorInvalidValue;
     // with ghosts every chunk's traced photons may each leave one ghost start in the list
     if ((L.flags & PHX_F_GHOSTS) && (!W.ghost_list || !W.ghost_ctr || W.ghost_cap < W.chunk))
@@ -2901,7 +3037,7 @@ hipError_t launch_trace(const DevParams* dparams, const Launch& L, const Workspa
 hipError_t launch_adjoint(const DevParams* dparams, const Launch& L, const Workspace& W, int n_cu,
                           const LaunchConfig& cfg, const Adjoint& A, double* colsum, double* grad,
                           hipStream_t stream, const Pipe& pipe, const Timing& T) {
-    const Stages S{dparams, L, W, n_cu, cfg, stream, pipe, T};
+    const Stages S{dparams, L, W, n_cu, cfg, stream, pipe, T, true};
     if (!S.valid()) return hipErrorInvalidValue;
     const uint64_t grid = (uint64_t)n_cu * A.per_cu;
     if (grid * kBlock > A.tape_stride) return hipErrorInvalidValue;

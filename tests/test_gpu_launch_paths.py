@@ -60,3 +60,40 @@ def test_launches_of_one_context_on_two_streams_wait_for_each_other(phx):
     torch.cuda.synchronize()
     assert torch.equal(images[0] + images[1], want)
     tr.close()
+
+
+@pytest.mark.parametrize("photons", [1, 255, 256, 257, 4097, (1 << 19) - 1, (1 << 19) + 1,
+                                     (1 << 20) + 63, (1 << 21) + 1, (1 << 22) + 5])
+@pytest.mark.parametrize("cull", [True, False])
+def test_lists_hold_every_photon_at_the_edges_of_ranges_and_of_the_sort(phx, photons, cull):
+    """The lists of photons to trace (unsorted and sorted, with the pre-roll and without, ranges of 256,
+    1024 and 4096) against phx_trace_noalloc, which never sorts and cuts chunks of 2^19: the same image,
+    and every photon in one place of the statistics."""
+    import torch
+    from paper_1504_06570_amd.scene import configs as C
+    scene = C.full(scale=1e-6, screen_n=64)
+    tr = phx.Tracer(scene)
+    flags = int(scene.physics) | (phx.F_CULL if cull else 0)
+    got, st, _, _ = tr.trace(flags=flags, stats=tr.new_stats(), photon_count=photons)
+    want, st2, _, _ = tr.trace(flags=flags, stats=tr.new_stats(), photon_count=photons, noalloc=True)
+    torch.cuda.synchronize()
+    assert torch.equal(got, want) and torch.equal(st, st2)
+    assert int(phx.stats_table(st).sum()) == photons
+    tr.close()
+
+
+def test_lists_of_many_sources_without_an_atmosphere(phx):
+    """A chunk of several sources above the sort's limit, classed only: the same image and moment words as
+    one launch per source (below the limit, unsorted)."""
+    import torch
+    from paper_1504_06570_amd.scene import configs as C
+    scene = C.telescope(scale=0.2)      # 441 sources, 2e6 photons
+    tr = phx.Tracer(scene)
+    m = tr.new_moments()
+    img = tr.trace(moments=m)[0]
+    ref, mr = tr.new_image(), tr.new_moments()
+    for s in range(0, 441, 63):
+        tr.trace(ref, moments=mr, src_begin=s, src_end=s + 63)
+    torch.cuda.synchronize()
+    assert torch.equal(img, ref) and torch.equal(m, mr)
+    tr.close()
