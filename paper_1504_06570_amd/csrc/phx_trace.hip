@@ -834,9 +834,8 @@ __device__ __forceinline__ double field_sigma(const DevParams& P, double depth, 
 // proportional to the drift distance to the collecting surface.  With PHX_F_DEAD_LAYER an
 // electron converted less than `dead` below the entrance surface is removed (section 2.4.2
 // field-free layer).  Moves (xc, yc) from the landing point to the electron position; returns 0,
-// PHX_ESCAPED or PHX_DEAD.  Inlined: it raises the optics kernel's spills (20 -> 65 words), but a
-// call would give the kernel a stack frame and register saves around it, which cost more
-// (headline step 49.9 -> 48.5 ms inlined).
+// PHX_ESCAPED or PHX_DEAD.  Inlined: a call would give the kernel a stack frame and register saves
+// around it.
 __device__ __forceinline__ int sensor_stage(const DevParams& P, const Launch& L, const Rng& rng,
                                          double lam, const double* d, double& xc, double& yc) {
     if (L.flags & PHX_F_SILICON) {
@@ -2127,11 +2126,11 @@ constexpr int kWaves = kBlock / 64;
 // time through ghost_ctr[1], with every lane refilled from the claimed entries as its photon is
 // settled.  Keeping the branches out of the sequential pass keeps its registers those of the
 // kernel without ghosts.
-// Register budget for three waves per SIMD (168 VGPRs): alone the kernel runs about 7 % slower
-// than with four (128 VGPRs and more spills), but beside the sky stage the whole step is faster,
-// the launch then placing fewer of its workgroups on a compute unit.
+// Four wavefronts per SIMD (128 VGPRs; without the compiler's hoisting of constants out of the loop the
+// kernel needs 119, with it 168 and spills): 8.6e6 photons 1.36 -> 1.04 ms with the compute units
+// full.
 template <bool ZERN, bool EXTRA, int GH>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 8))) void back_kernel(
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) void back_kernel(
         const DevParams* __restrict__ Pg, const Launch L, uint64_t begin,
         const uint32_t* __restrict__ surv, const unsigned int* __restrict__ count, uint64_t n_all,
         const double* __restrict__ st, uint64_t st_stride, unsigned long long* unit_ctr,
@@ -2936,7 +2935,7 @@ struct Stages {
             sort_photons(W, sp, c, seg_buf(c), seg_n_buf(c), surv_buf(c), stable, stream);
             mark(3, 1, stream);
         }
-        const dim3 fg = grid_of((sp.len + kBlock - 1) / kBlock, n_cu, cfg.front_per_cu);
+        const dim3 fg = grid_of((sp.len + kBlock - 1) / kBlock, n_cu, kGroupsPerUnit * cfg.front_per_cu);
         // the dies take a pupil sector each (a grid that covers them evenly, the static schedule)
         const uint32_t* sect = sorted(c) && (L.flags & PHX_F_ATMOSPHERE) && !ft &&
                                        fg.x % kSectors == 0 ? W.sect + 16 * c : nullptr;
@@ -3032,7 +3031,7 @@ hipError_t launch_trace(const DevParams* dparams, const Launch& L, const Workspa
     S.run(n_chunks, cfg.dynamic != 0, [&](uint64_t c, hipStream_t bs) {
         const ChunkSpan& sp = W.plan[c];
         const uint64_t want = (sp.len + kBlock - 1) / kBlock;
-        const uint64_t bcap = (uint64_t)n_cu * cfg.back_per_cu;
+        const uint64_t bcap = (uint64_t)n_cu * kGroupsPerUnit * cfg.back_per_cu;
         const dim3 bg((unsigned)(want < bcap ? want : bcap));
         unsigned long long* bt = cfg.dynamic ? W.tiles + 2 * c + 1 : nullptr;
         S.mark(2, 0, bs);
