@@ -318,6 +318,10 @@ hipError_t launch_adjoint(const DevParams* dparams, const Launch& L, const Works
                           hipStream_t stream, const Pipe& pipe, const Timing& T);
 // One readout of a sensor image (phx_readout): parameters, the input electrons and the
 // buffers of each step (device pointers).
+struct ReadoutThr {
+    uint32_t a0, a1;    // a draw's word above a0 is a delay, above a1 one of two slots or more
+    double p0;          // probability of no delay
+};
 struct ReadoutJob {
     phx_readout_params p;
     const uint32_t* in;
@@ -326,9 +330,10 @@ struct ReadoutJob {
     uint32_t* par;      // [amp][sh + over_y][sw] after the parallel transfers
     uint32_t* ser;      // [amp][sh + over_y][sw + over_x] after the serial transfers
     uint16_t* out;      // [amp][sh + over_y][sw + over_x] ADU
-    uint32_t* heavy;    // packets with many electrons, handled one workgroup each
+    uint32_t* heavy;    // packets with many electrons, handled by whole wavefronts
                         // [max(ny nx, amp (sh + over_y) sw)]
-    uint32_t* heavy_count;
+    uint32_t* heavy_count;   // [2] of the parallel and the serial transfers
+    ReadoutThr* thr;    // [sh + sw] of the transfer counts 1..sh (parallel) and 1..sw (serial)
 };
 hipError_t launch_readout(const ReadoutJob& J, hipStream_t stream);
 

@@ -113,3 +113,30 @@ def test_readout_error_paths(phx):
         with pytest.raises(phx.PhxError):
             tr.readout(img, Readout(amp_nx=2, amp_ny=2).replace(**bad))
     tr.close()
+
+
+@pytest.mark.parametrize("shape,over", [
+    ((3, 130), dict(amp_nx=1, amp_ny=1)),                                      # less than a workgroup
+    ((66, 514), dict(amp_nx=2, amp_ny=2, over_x=1, over_y=65)),
+    ((4, 8200), dict(amp_nx=4, amp_ny=2)),                                     # half-rows beyond LDS
+    ((128, 128), dict(cte_parallel=0.5, cte_serial=0.6)),                      # no word is kept
+    ((64, 256), dict(cte_parallel=1.0, cte_serial=1.0)),
+    ((64, 256), dict(nonlinearity=3.0, read_noise=(4000.0,) * 32)),            # bounds do not hold
+    ((64, 256), dict(bit_sigma=(0.3,) * 16, read_noise=(0.0,) * 32)),
+    ((64, 256), dict(bit_sigma=(0.0,) * 15 + (0.01,), bias=(-50.0,) * 32)),    # clamped values
+    ((2, 64), dict(dark_rate=1e3, full_well=1e7, hot_fraction=0.0, hot_column_fraction=0.0)),
+])
+def test_readout_at_the_edges_of_its_kernels(phx, shape, over):
+    """Packets at the limits of the light and heavy transfers (64 electrons) and of a wavefront's draw
+    blocks (256), ragged sizes, transfer probabilities that leave no word or every word, and values for
+    which the deviates in 32 bits decide nothing: the electrons of every stage and the converted
+    values are the oracle's."""
+    rp = Readout(**{**dict(amp_nx=4, amp_ny=2, over_x=3, over_y=2, hot_fraction=1e-3,
+                           dead_fraction=1e-3, hot_column_fraction=1e-3, cte_parallel=1 - 1e-4,
+                           cte_serial=1 - 5e-5), **over})
+    img = _image(*shape)
+    edge = np.array([0, 1, 3, 4, 5, 63, 64, 65, 255, 256, 257, 1023, 1024, 1025, 100000, 100001],
+                    np.uint32)
+    img[:2, 8:24] = edge
+    g, o = run_both(phx, img, rp)
+    assert check(g, o) <= 2
