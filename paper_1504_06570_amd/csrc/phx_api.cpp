@@ -1373,20 +1373,21 @@ phx_status prepare(phx_ctx c, const phx_trace_args* a, hipStream_t st, phx::Laun
                        (unsigned long long*)c->d_tiles, c->d_seg, c->d_seg_n, c->d_hist, c->d_sect,
                        c->plan.data(), (uint64_t)c->plan.size(), 2};
     if (a->flags & PHX_F_GHOSTS) {
-        // every traced photon of a chunk may leave one ghost start: a list of chunk entries
+        // every traced photon of a chunk may leave one ghost start: a list of ghost_entries
         // (14 doubles each; 7.5 GB for chunks of 2^26 photons); grows only
-        if (chunk > c->ghost_cap || !c->d_ghost_ctr) {
+        const uint64_t entries = phx::ghost_entries(chunk, c->n_cu, c->cfg.back_per_cu);
+        if (entries > c->ghost_cap || !c->d_ghost_ctr) {
             hipError_t e = hipStreamSynchronize(st);
             if (e != hipSuccess) return hip_fail(c, e, "hipStreamSynchronize");
             free_dev(c->d_ghost);
             c->ghost_cap = 0;
             c->graphs_clear();
-            e = hipMalloc((void**)&c->d_ghost, chunk * phx::kGhostFields * sizeof(double));
+            e = hipMalloc((void**)&c->d_ghost, entries * phx::kGhostFields * sizeof(double));
             if (e == hipSuccess && !c->d_ghost_ctr)
                 e = hipMalloc((void**)&c->d_ghost_ctr, 2 * sizeof(unsigned long long));
             if (e != hipSuccess) return fail(c, PHX_ERR_NOMEM, "ghost list: %s",
                                              hipGetErrorString(e));
-            c->ghost_cap = chunk;
+            c->ghost_cap = entries;
         }
         W.ghost_list = c->d_ghost;
         W.ghost_cap = c->ghost_cap;

@@ -191,7 +191,7 @@ struct Workspace {
     uint64_t n_plan;
     int buffers;               // lists and states hold this many chunks (1 or 2)
     double* ghost_list = nullptr;          // [kGhostFields][ghost_cap] ghost starts of a chunk
-    uint64_t ghost_cap = 0;                 // (with ghosts: at least chunk entries)
+    uint64_t ghost_cap = 0;                 // (with ghosts: at least ghost_entries)
     unsigned long long* ghost_ctr = nullptr; // [2] entries listed, entries claimed
 };
 // Photons per pre-roll range (one workgroup's unit): 4096 amortise the range's barriers and keep
@@ -285,6 +285,16 @@ constexpr int kTileIters = 8;
 // path (the other instantiations hold none of its code).
 constexpr uint32_t kFrontExtra = PHX_F_DISPERSION | PHX_F_DOME | PHX_F_HALO | PHX_F_SECOND_KICK;
 constexpr uint32_t kBackExtra = PHX_F_AEROSOL | PHX_F_SPIDER | PHX_F_GHOSTS;
+
+// Ghost list: a wavefront of the sequential pass reserves kGhostReserve entries at a time (at least 64), one
+// of the branch pass claims kGhostClaim.  The list holds an entry for each photon of a chunk and the
+// entries that the wavefronts leave unused.
+constexpr uint64_t kGhostReserve = 128, kGhostClaim = 64;
+constexpr uint64_t ghost_entries(uint64_t chunk, int n_cu, int back_per_cu) {
+    const uint64_t launched = (uint64_t)n_cu * kGroupsPerUnit * back_per_cu * (kThreads / 64);
+    const uint64_t filled = chunk / 64 + kThreads / 64;   // no more workgroups than units of work
+    return chunk + kGhostReserve * (launched < filled ? launched : filled);
+}
 
 // Optional per-kernel timing: events recorded before/after each kernel launch.
 struct Timing {

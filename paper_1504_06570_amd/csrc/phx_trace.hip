@@ -1093,47 +1093,75 @@ __device__ __forceinline__ void ghost_get(const double* q, uint64_t cap, uint64_
     newton = (int)(uint32_t)kn;
     r = (uint32_t)__double_as_longlong(f[13 * cap]);
 }
-// Where the sequential pass leaves a lane's ghost start: the hit's fields are written to the
-// lane's column of the wavefront's LDS staging area at the reflecting surface (field i at
-// f[i * 64]), so that no register carries them out of the surface loop, and k records the
-// surface (-1: none).
-constexpr int kGhostStage = 11;   // q, d, N, dn, index of the medium
+// Where the sequential pass leaves a lane's ghost start: the hit's fields are written to LDS at the
+// reflecting surface, so that no register carries them out of the surface loop, and k records the
+// surface (-1: none).  The first seven go to an entry of the wavefront's queue that is free at the
+// time (field i at f[i * kQueue]), the others to the lane's column of a staging area (at g[i * 64]): with
+// all in an area of their own two workgroups fitted a compute unit, now three (2.6e7 photons
+// 3.0 -> 2.9 ms).
+constexpr int kQueue = 128;               // queued photons per wavefront (64 + 63 carried)
+constexpr int kGhostQueued = 7;           // q, d, N_x
+constexpr int kGhostStage = 4;            // N_y, N_z, dn, index of the medium
 struct GhostSink {
     double* f;
+    double* g;
     int k;
 };
 __device__ __forceinline__ void ghost_stage(GhostSink* gs, const Hit& h, int k, double n_cur) {
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
-        gs->f[(0 + i) * 64] = h.q[i];
-        gs->f[(3 + i) * 64] = h.d[i];
-        gs->f[(6 + i) * 64] = h.N[i];
+        gs->f[(0 + i) * kQueue] = h.q[i];
+        gs->f[(3 + i) * kQueue] = h.d[i];
     }
-    gs->f[9 * 64] = h.dn;
-    gs->f[10 * 64] = n_cur;
+    gs->f[6 * kQueue] = h.N[0];
+    gs->g[0 * 64] = h.N[1];
+    gs->g[1 * 64] = h.N[2];
+    gs->g[2 * 64] = h.dn;
+    gs->g[3 * 64] = n_cur;
     gs->k = k;
 }
-// Appends the lanes holding a ghost start (gs.k >= 0) to the list (ctr[0] counts the entries;
-// an entry beyond cap, which the list's size rules out, is not written).  Every lane of the
-// wavefront must call it.
+// Appends the lanes holding a ghost start (gs.k >= 0) to the list.  A wavefront reserves
+// kGhostReserve entries at a time (ctr[0] counts the reserved ones; an entry beyond cap, which the
+// list's size rules out, is not written): an atomic for each append, all on one address, held the pass
+// up (2.6e7 photons 2.9 ms, now 2.35; the unused entries cost the branch pass 0.3 of its 4.7).  Every lane of the wavefront must call it.
+struct GhostRoom {
+    uint64_t next, end;   // the wavefront's reserved, not yet written entries
+};
 __device__ __forceinline__ void ghost_append(double* q, uint64_t cap, unsigned long long* ctr,
-                                             const GhostSink& gs, const Outcome& o, uint32_t r) {
+                                             GhostRoom& room, const GhostSink& gs, const Outcome& o,
+                                             uint32_t r) {
     const bool pend = gs.k >= 0;
     const uint64_t pm = __ballot(pend);
     if (!pm) return;
-    unsigned long long base = 0;
-    if (__lane_id() == 0) base = atomicAdd(&ctr[0], (unsigned long long)__popcll(pm));
-    base = __shfl(base, 0);
-    const uint64_t e = base + __popcll(pm & ((1ull << __lane_id()) - 1ull));
+    const uint64_t n = (uint64_t)__popcll(pm), avail = room.end - room.next;
+    const uint64_t rank = (uint64_t)__popcll(pm & ((1ull << __lane_id()) - 1ull));
+    uint64_t e = room.next + rank;
+    if (n > avail) {
+        unsigned long long b = 0;
+        if (__lane_id() == 0) b = atomicAdd(&ctr[0], (unsigned long long)kGhostReserve);
+        b = __shfl(b, 0);
+        if (rank >= avail) e = b + (rank - avail);
+        room.next = b + (n - avail);
+        room.end = b + kGhostReserve;
+    } else {
+        room.next += n;
+    }
     if (pend && e < cap) {
         double* f = q + e;
 #pragma unroll
-        for (int i = 0; i < kGhostStage; ++i) f[i * cap] = gs.f[i * 64];
+        for (int i = 0; i < kGhostQueued; ++i) f[i * cap] = gs.f[i * kQueue];
+#pragma unroll
+        for (int i = 0; i < kGhostStage; ++i) f[(kGhostQueued + i) * cap] = gs.g[i * 64];
         f[11 * cap] = o.lam;
         f[12 * cap] = __longlong_as_double((long long)(((uint64_t)(uint32_t)gs.k << 32) |
                                                        (uint32_t)o.newton));
         f[13 * cap] = __longlong_as_double((long long)r);
     }
+}
+// The entries that stay unused at the wavefront's end: surface -1.
+__device__ __forceinline__ void ghost_close(double* q, uint64_t cap, const GhostRoom& room) {
+    for (uint64_t e = room.next + __lane_id(); e < room.end && e < cap; e += 64)
+        q[12 * cap + e] = __longlong_as_double(-1ll);
 }
 
 template <bool ZERN, bool TAPE = false, bool GHOST = false>
@@ -2117,13 +2145,12 @@ __device__ __forceinline__ void book(const DevParams& P, const Launch& L, bool a
 // through the remaining surfaces.  Work units of 64 photons: static (unit w of the grid's
 // wavefronts, then every grid-size-th unit) or from a device counter.
 constexpr int kWin = 32;                  // LDS pixel window of the optics kernel
-constexpr int kQueue = 128;               // queued photons per wavefront (64 + 63 carried)
 constexpr int kWaves = kBlock / 64;
 // EXTRA: aerosol and the spider at the entrance.  GH, the ghost branch of the roulette (with
 // ghosts the kernel runs twice per chunk): 0 none; 1 the sequential pass, which appends the
 // photons a coating reflects to the chunk's ghost list (ghost_list, cap entries, ghost_ctr[0]
-// their number) instead of booking them; 2 the branches of the listed photons, claimed 64 at a
-// time through ghost_ctr[1], with every lane refilled from the claimed entries as its photon is
+// their number) instead of booking them; 2 the branches of the listed photons, claimed
+// kGhostClaim at a time through ghost_ctr[1], with every lane refilled from the claimed entries as its photon is
 // settled.  Keeping the branches out of the sequential pass keeps its registers those of the
 // kernel without ghosts.
 // Four wavefronts per SIMD (128 VGPRs; without the compiler's hoisting of constants out of the loop the
@@ -2143,7 +2170,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) 
     __shared__ double s_q[kWaves][7][kQueue];   // p, n (global frame) and wavelength
     __shared__ uint32_t s_qr[kWaves][kQueue];   // position in the survivor list
     __shared__ int32_t s_qk[kWaves][kQueue];    // Newton steps so far
-    // GH == 1: each wavefront's staging area of ghost starts (kGhostStage fields x 64 lanes)
+    // GH == 1: each wavefront's staging area of ghost starts (kGhostStage fields x 64 lanes; the
+    // other fields go to the queue: to the lane's own entry, once read, in the second pass, to the upper
+    // half, free then, in the first)
     __shared__ double s_gs[GH == 1 ? kWaves * kGhostStage * 64 : 1];
     for (int i = threadIdx.x; i < kWin * kWin; i += blockDim.x) s_win[i] = 0;
     if (threadIdx.x == 0) s_org = -1;
@@ -2168,7 +2197,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) 
     int qn = 0;                                // queued photons (wavefront-uniform)
     uint32_t newton = 0, traced = 0;
     if (GH == 2) {
-        // the branches: the wavefront claims 64 listed starts at a time; a lane whose photon is
+        // the branches: the wavefront claims kGhostClaim listed starts at a time; a lane whose photon is
         // settled takes the next claimed start, so that the lanes stay busy until the list is
         // exhausted
         const uint64_t total = min((uint64_t)ghost_ctr[0], ghost_cap);
@@ -2186,10 +2215,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) 
             const uint64_t idle = __ballot(!busy);
             if (claims && idle && wbase == wend) {
                 unsigned long long b = 0;
-                if (lane == 0) b = atomicAdd(&ghost_ctr[1], 64ull);
+                if (lane == 0) b = atomicAdd(&ghost_ctr[1], (unsigned long long)kGhostClaim);
                 b = __shfl(b, 0);
                 wbase = b < total ? b : total;
-                wend = b + 64 < total ? b + 64 : total;
+                wend = b + kGhostClaim < total ? b + kGhostClaim : total;
                 claims = wbase < wend;
             }
             const uint64_t avail = wend - wbase;
@@ -2201,17 +2230,22 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) 
                 uint32_t r;
                 int nw;
                 ghost_get(ghost_list, ghost_cap, wbase + rank, gs, lam, r, nw);
-                g = begin + (surv ? (uint64_t)surv[r] : (uint64_t)r);
-                decode(L, g, si, idx);
-                rng = Rng{L.seed, (uint32_t)si, (uint32_t)idx, (uint32_t)(idx >> 32)};
-                outcome_init(o, lam);
-                o.newton = nw;
-                oc = optics_of(P, L, lam);
-                ghost_begin(P, gs.h, gs.k, gs.n_cur, gr);
-                busy = true;
+                if (gs.k >= 0) {   // not an unused entry
+                    g = begin + (surv ? (uint64_t)surv[r] : (uint64_t)r);
+                    decode(L, g, si, idx);
+                    rng = Rng{L.seed, (uint32_t)si, (uint32_t)idx, (uint32_t)(idx >> 32)};
+                    outcome_init(o, lam);
+                    o.newton = nw;
+                    oc = optics_of(P, L, lam);
+                    ghost_begin(P, gs.h, gs.k, gs.n_cur, gr);
+                    busy = true;
+                }
             }
             wbase += take;
-            if (__ballot(busy) == 0) break;
+            if (__ballot(busy) == 0) {   // nothing left, or only unused entries taken
+                if (wbase == wend && !claims) break;
+                continue;
+            }
             bool fin = false;
             if (busy) fin = ghost_step<ZERN>(P, L, rng, oc, gr, o);
             if (fin) {
@@ -2221,6 +2255,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) 
             book(P, L, fin, g, si, idx, o, s_stats, s_win, kWin, &s_org, &s_mc);
         }
     }
+    GhostRoom room{0, 0};
     for (;;) {
         if (GH == 2) break;
         const bool more = unit < n_units;
@@ -2233,7 +2268,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) 
             uint64_t g = 0, idx = 0;
             int si = 0;
             uint32_t r = 0;
-            GhostSink gs{s_gs + (GH == 1 ? wave * kGhostStage * 64 + lane : 0), -1};
+            GhostSink gs{&q[0][max(qn - take + lane, 0)],
+                         s_gs + (GH == 1 ? wave * kGhostStage * 64 + lane : 0), -1};
             if (act) {
                 const int e = qn - take + lane;
                 r = qr[e];
@@ -2254,7 +2290,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) 
                                                         nullptr, 0, gp);
             }
             const bool fin = act && !(GHOST && gs.k >= 0);
-            if (GHOST) ghost_append(ghost_list, ghost_cap, ghost_ctr, gs, o, r);
+            if (GHOST) ghost_append(ghost_list, ghost_cap, ghost_ctr, room, gs, o, r);
             if (fin) newton += o.newton;
             book(P, L, fin, g, si, idx, o, s_stats, s_win, kWin, &s_org, &s_mc);
             qn -= take;
@@ -2271,7 +2307,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) 
         uint64_t g = 0, idx = 0;
         int si = 0;
         Ray ray{{0.0, 0.0, 0.0}, {0.0, 0.0, 1.0}};
-        GhostSink gs{s_gs + (GH == 1 ? wave * kGhostStage * 64 + lane : 0), -1};
+        GhostSink gs{&q[0][64 + lane], s_gs + (GH == 1 ? wave * kGhostStage * 64 + lane : 0), -1};
         if (valid) {
             g = begin + (surv ? (uint64_t)surv[r] : r);
             decode(L, g, si, idx);
@@ -2294,7 +2330,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) 
             }
             traced += 1;
         }
-        if (GHOST) ghost_append(ghost_list, ghost_cap, ghost_ctr, gs, o, (uint32_t)r);
+        if (GHOST) {
+            ghost_append(ghost_list, ghost_cap, ghost_ctr, room, gs, o, (uint32_t)r);
+            __builtin_amdgcn_wave_barrier();   // before the queue's upper half is written again
+        }
         const uint64_t am = __ballot(alive);
         if (alive) {
             const int e = qn + __popcll(am & ((1ull << lane) - 1ull));
@@ -2317,6 +2356,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) 
         }
         __builtin_amdgcn_wave_barrier();
     }
+    if (GHOST) ghost_close(ghost_list, ghost_cap, room);
     stats_flush(L, s_stats, newton, traced);   // ends with a barrier
     if (threadIdx.x == 0 && (L.flags & PHX_F_MOMENTS)) moment_cache_flush(L, &s_mc);
     const int org = s_org;
@@ -3027,7 +3067,8 @@ hipError_t launch_trace(const DevParams* dparams, const Launch& L, const Workspa
     const Stages S{dparams, L, W, n_cu, cfg, stream, pipe, T, false};
     if (!S.valid()) return hipErrorInvalidValue;
     // with ghosts every chunk's traced photons may each leave one ghost start in the list
-    if ((L.flags & PHX_F_GHOSTS) && (!W.ghost_list || !W.ghost_ctr || W.ghost_cap < W.chunk))
+    if ((L.flags & PHX_F_GHOSTS) && (!W.ghost_list || !W.ghost_ctr ||
+                                      W.ghost_cap < ghost_entries(W.chunk, n_cu, cfg.back_per_cu)))
         return hipErrorInvalidValue;
     const uint64_t n_chunks = W.n_plan;
     if (cfg.dynamic)
