@@ -6,6 +6,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <limits>
 #include <map>
 #include <string>
 #include <vector>
@@ -552,9 +553,7 @@ phx_status phx_load_prescription(phx_ctx c, const phx_prescription* p) {
     H.chip_x0 = p->chip_x0;
     H.chip_y0 = p->chip_y0;
     H.pixel = p->pixel;
-    H.inv_pixel = 1.0 / p->pixel;
     H.t_si = p->si_thickness;
-    H.inv_t_si = 1.0 / p->si_thickness;
     H.sigma_max = p->sigma_max;
     // Rajkanan temperature-dependent constants (section 2.4.2)
     const double T = p->si_temperature, kB = 8.617333262e-5;
@@ -568,6 +567,9 @@ phx_status phx_load_prescription(phx_ctx c, const phx_prescription* p) {
         H.emit[i] = 1.0 - std::exp(-ep[i] / (kB * T));
         H.inv_absorb[i] = 1.0 / H.absorb[i];
         H.inv_emit[i] = 1.0 / H.emit[i];
+        // below 0.95 K the divisor is infinite and its term zero: so that the device's quotient by a
+        // reciprocal gives 0 too (see absorption)
+        if (!std::isfinite(H.absorb[i])) H.absorb[i] = std::numeric_limits<double>::max();
     }
     build_surfaces(c);
     c->have_presc = true;

@@ -94,11 +94,11 @@ struct DevParams {
     double z_start, obsc_z, obsc_r;
     double obsc_s;             // smallest s with sqrt(s) >= obsc_r
     double sell_b[3], sell_c[3];
-    double chip_x0, chip_y0, pixel, inv_pixel;
+    double chip_x0, chip_y0, pixel;
     double t_si, sigma_max;
     // Rajkanan constants at the device temperature (section 2.4.2)
     double eg[2], egd, absorb[2], emit[2];
-    double inv_absorb[2], inv_emit[2], inv_t_si;
+    double inv_absorb[2], inv_emit[2];
     // coatings: uniform grid in s = sin^2(theta) and wavelength
     double inv_s_step, lam0, inv_dlam;
     int32_t cull_order[PHX_MAX_SURF]; // coated surfaces, most selective coating first
