@@ -1638,6 +1638,9 @@ phx_status phx_adjoint_moments(phx_ctx c, const phx_trace_args* a, const uint64_
     if (set_device(c) != PHX_OK) return PHX_ERR_HIP;
     hipStream_t st = (hipStream_t)stream;
     const uint64_t n = (uint64_t)(a->src_end - a->src_begin);
+    // the coefficients are the context's: an earlier call's adjoint may still read them
+    phx_status r = order_begin(c, st);
+    if (r != PHX_OK) return r;
     if (n > c->seed_cap) {
         hipError_t e = hipStreamSynchronize(st);
         if (e != hipSuccess) return hip_fail(c, e, "hipStreamSynchronize");
@@ -1651,7 +1654,9 @@ phx_status phx_adjoint_moments(phx_ctx c, const phx_trace_args* a, const uint64_
                                          (size_t)a->src_begin * PHX_MOMENT_WORDS,
                                      (int)n, dmom_dev, c->d_seed, st);
     if (e != hipSuccess) return hip_fail(c, e, "seed kernel launch");
-    return phx_adjoint(c, a, c->d_seed, grad_dev, jac_dev, jac_stride, jac_capacity, stream);
+    r = phx_adjoint(c, a, c->d_seed, grad_dev, jac_dev, jac_stride, jac_capacity, stream);
+    if (r != PHX_OK) (void)order_end(c, st);   // the seed kernel is on its way
+    return r;
 }
 
 phx_status phx_moments(phx_ctx c, const uint64_t* moments_dev, int32_t n_src, double* out_dev,
