@@ -1875,6 +1875,8 @@ phx_status phx_readout(phx_ctx c, const phx_readout_params* p, const uint32_t* i
                     (unsigned long long)adu_capacity, (unsigned long long)need[2]);
     if (set_device(c) != PHX_OK) return PHX_ERR_HIP;
     hipStream_t st = (hipStream_t)stream;
+    const phx_status r = order_begin(c, st);   // the scratch is the context's
+    if (r != PHX_OK) return r;
     uint32_t* bufs[4] = {work, par, ser, nullptr};
     for (int k = 0; k < 4; ++k) {
         if (bufs[k]) continue;
@@ -1907,8 +1909,8 @@ phx_status phx_readout(phx_ctx c, const phx_readout_params* p, const uint32_t* i
     J.thr = (phx::ReadoutThr*)(bufs[3] + 4);
     J.heavy = bufs[3] + 4 + thr_words;
     const hipError_t e = phx::launch_readout(J, st);
-    if (e != hipSuccess) return hip_fail(c, e, "readout launch");
-    return PHX_OK;
+    const phx_status q = order_end(c, st);
+    return e == hipSuccess ? q : hip_fail(c, e, "readout launch");
 }
 
 phx_status phx_set_timing(phx_ctx c, int32_t on) {

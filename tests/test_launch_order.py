@@ -11,6 +11,7 @@ import pytest
 from paper_1504_06570_amd import phx
 from paper_1504_06570_amd.scene import coatings
 from paper_1504_06570_amd.scene import configs
+from paper_1504_06570_amd.scene.readout import Readout
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -34,7 +35,8 @@ class Recorded:
                                             coatings.DLAM))
         self.load_sources()
         self.memory = np.zeros(1 << 16)          # any output buffer: nothing writes to it
-        self.image = np.zeros((64, 64), np.uint32)
+        self.image = np.zeros((128, 128), np.uint32)
+        self.readout = phx.readout_struct(Readout(amp_nx=2, amp_ny=2))
         self.adu = np.zeros(1 << 16, np.uint16)
         self.L.rec_reset()
 
@@ -70,6 +72,11 @@ class Recorded:
         elif name == "adjoint_moments":
             self.check(self.L.phx_adjoint_moments(self.ctx, C.byref(self.args(photons)), m, m, m, None,
                                                   0, 0, st))
+        elif name == "readout":
+            side = 64 if photons <= 1000 else 128
+            self.check(self.L.phx_readout(self.ctx, C.byref(self.readout), self.image.ctypes.data, side,
+                                          side, self.adu.ctypes.data, self.adu.size, None, None, None,
+                                          st))
 
     def overlaps(self):
         return self.L.rec_overlaps().decode()
@@ -93,7 +100,7 @@ def rec(library, monkeypatch):
     r.L.phx_destroy(r.ctx)
 
 
-CALLS = ["trace", "trace_batched", "adjoint", "adjoint_moments"]
+CALLS = ["trace", "trace_batched", "adjoint", "adjoint_moments", "readout"]
 
 
 @pytest.mark.parametrize("first,second", list(itertools.product(CALLS, CALLS)))
