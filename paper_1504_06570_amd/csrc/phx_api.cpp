@@ -437,21 +437,22 @@ phx_status phx_create(int32_t device, phx_ctx* out) {
         e = hipGetDeviceProperties(&prop, device);
         if (e == hipSuccess) c->n_cu = prop.multiProcessorCount;
     }
+    if (e == hipSuccess) e = hipEventCreateWithFlags(&c->order_ev, hipEventDisableTiming);
     if (e == hipSuccess) e = hipMalloc((void**)&c->dparams, sizeof(DevParams));
     // the device address of this GPU's phx_trace_noalloc workspace (looked up once per device,
     // with the device current)
     if (e == hipSuccess) e = phx::scratch_address(device, &c->scratch);
-    if (e != hipSuccess) {
-        free_dev(c->dparams);
-        delete c;
-        return PHX_ERR_HIP;
-    }
+    phx_status r = e == hipSuccess ? PHX_OK : PHX_ERR_HIP;
     try {
         c->plan.reserve(phx::kNoAllocMaxChunks);
     } catch (...) {
+        if (r == PHX_OK) r = PHX_ERR_NOMEM;
+    }
+    if (r != PHX_OK) {
+        if (c->order_ev) (void)hipEventDestroy(c->order_ev);
         free_dev(c->dparams);
         delete c;
-        return PHX_ERR_NOMEM;
+        return r;
     }
     *out = c;
     return PHX_OK;
@@ -1244,24 +1245,23 @@ uint64_t make_plan(phx_ctx c, const phx_trace_args* a, const phx::Launch& L, uin
     return n;
 }
 
-// Launches of one context share its workspace, so a launch waits for the one before it, whichever
-// stream that was on: order_end records an event behind a launch and order_begin makes the next
-// launch's stream wait for it (free on the same stream; the record takes the host 4 us).  A stream
-// that is being captured does neither: its launches run when the graph does.
+// Launches of one context share its workspace and parameter block, so a launch waits for the one
+// before it, whichever stream that was on: order_end records an event behind a launch and
+// order_begin, ahead of all that a call enqueues or frees, makes its stream wait for it (free on
+// the same stream; the record takes the host 4 us).  A stream that is being captured does neither:
+// its launches run when the graph does.
 bool capturing(hipStream_t st) {
     hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
     return hipStreamIsCapturing(st, &s) == hipSuccess && s != hipStreamCaptureStatusNone;
 }
 phx_status order_begin(phx_ctx c, hipStream_t st) {
-    if (!c->order_ev || capturing(st)) return PHX_OK;
+    if (capturing(st)) return PHX_OK;
     const hipError_t e = hipStreamWaitEvent(st, c->order_ev, 0);
     return e == hipSuccess ? PHX_OK : hip_fail(c, e, "hipStreamWaitEvent");
 }
 phx_status order_end(phx_ctx c, hipStream_t st) {
     if (capturing(st)) return PHX_OK;
-    hipError_t e = hipSuccess;
-    if (!c->order_ev) e = hipEventCreateWithFlags(&c->order_ev, hipEventDisableTiming);
-    if (e == hipSuccess) e = hipEventRecord(c->order_ev, st);
+    const hipError_t e = hipEventRecord(c->order_ev, st);
     return e == hipSuccess ? PHX_OK : hip_fail(c, e, "hipEventRecord");
 }
 
@@ -1445,8 +1445,10 @@ phx_status phx_trace(phx_ctx c, const phx_trace_args* a, void* stream) {
     phx::Launch L;
     phx::Workspace W;
     phx_status r = prepare(c, a, st, L, W);
-    if (r == PHX_OK) r = enqueue(c, L, W, st, true);
-    return r == PHX_OK ? order_end(c, st) : r;
+    if (r != PHX_OK) return r;
+    r = enqueue(c, L, W, st, true);
+    const phx_status q = order_end(c, st);
+    return r == PHX_OK ? q : r;
 }
 
 phx_status phx_trace_noalloc(phx_ctx c, const phx_trace_args* a, void* stream) {
@@ -1462,7 +1464,9 @@ phx_status phx_trace_noalloc(phx_ctx c, const phx_trace_args* a, void* stream) {
         return fail(c, PHX_ERR_CAPACITY, "phx_trace_noalloc traces at most %d sources, not %d",
                     phx::kNoAllocMaxSources, L.n_src);
     if (!c->scratch) return fail(c, PHX_ERR_STATE, "no scratch address for this device");
-    if (L.total == 0) return upload_params(c, st);
+    r = order_begin(c, st);
+    if (r != PHX_OK) return r;
+    if (L.total == 0) return upload_params(c, st);   // complete when it returns
     uint64_t chunk = 1024;
     const uint64_t max_chunk = 1ull << std::min(c->chunk_log2, phx::kNoAllocChunkLog2);
     while (chunk < L.total && chunk < max_chunk) chunk <<= 1;
@@ -1498,8 +1502,8 @@ phx_status phx_trace_noalloc(phx_ctx c, const phx_trace_args* a, void* stream) {
     // every stage on the caller's stream, one buffer set, no timing events
     const hipError_t e = phx::launch_trace(c->dparams, L, W, c->n_cu, c->cfg, st, phx::Pipe{},
                                            phx::Timing{});
-    if (e != hipSuccess) return hip_fail(c, e, "trace kernel launch");
-    return PHX_OK;
+    const phx_status q = order_end(c, st);
+    return e == hipSuccess ? q : hip_fail(c, e, "trace kernel launch");
 }
 
 phx_status phx_trace_batched(phx_ctx c, const phx_trace_args* a, void* stream) {
@@ -1620,8 +1624,8 @@ phx_status phx_adjoint(phx_ctx c, const phx_trace_args* a, const double* seed_de
     T.self = c;
     hipError_t e = phx::launch_adjoint(c->dparams, L, W, c->n_cu, c->cfg, A, c->d_colsum, grad_dev,
                                        st, pipe_of(c), T);
-    if (e != hipSuccess) return hip_fail(c, e, "adjoint kernel launch");
-    return order_end(c, st);
+    const phx_status q = order_end(c, st);
+    return e == hipSuccess ? q : hip_fail(c, e, "adjoint kernel launch");
 }
 
 phx_status phx_adjoint_moments(phx_ctx c, const phx_trace_args* a, const uint64_t* moments_dev,

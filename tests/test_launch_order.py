@@ -100,7 +100,7 @@ def rec(library, monkeypatch):
     r.L.phx_destroy(r.ctx)
 
 
-CALLS = ["trace", "trace_batched", "adjoint", "adjoint_moments", "readout"]
+CALLS = ["trace", "trace_batched", "adjoint", "adjoint_moments", "readout", "trace_noalloc"]
 
 
 @pytest.mark.parametrize("first,second", list(itertools.product(CALLS, CALLS)))
@@ -134,3 +134,13 @@ def test_a_captured_stream_gets_no_events(rec, name):
     rec.call(name, 0x22)
     rec.L.rec_capture(0x22, 0)
     assert rec.L.rec_capture_events() == 0
+
+
+def test_the_call_without_allocation_makes_nothing(rec):
+    """phx_trace_noalloc as the context's first launch and after others: no memory, stream or event."""
+    rec.call("trace_noalloc", 0x11)
+    assert rec.L.rec_resources() == 0
+    rec.call("trace", 0x22)
+    before = rec.L.rec_resources()
+    rec.call("trace_noalloc", 0x11, 100000)
+    assert rec.L.rec_resources() == before and rec.overlaps() == ""
