@@ -400,6 +400,13 @@ phx_status set_device(phx_ctx c) {
     return e == hipSuccess ? PHX_OK : hip_fail(c, e, "hipSetDevice");
 }
 
+// Before a table that launches read is overwritten in place: the context's last launch is complete
+// (a copy of the null stream does not wait for other streams).
+phx_status order_wait(phx_ctx c) {
+    const hipError_t e = hipEventSynchronize(c->order_ev);
+    return e == hipSuccess ? PHX_OK : hip_fail(c, e, "hipEventSynchronize");
+}
+
 phx_status upload_params(phx_ctx c, hipStream_t stream) {
     if (!c->dirty) return PHX_OK;
     for (int k = 0; k < c->host.n_surf; ++k) {
@@ -805,6 +812,8 @@ phx_status phx_load_physics(phx_ctx c, const phx_physics* x) {
         X.sig2_inv_step = N / dmax;
     }
     if (set_device(c) != PHX_OK) return PHX_ERR_HIP;
+    const phx_status w = order_wait(c);
+    if (w != PHX_OK) return w;
     if (!c->d_sig2) {
         const hipError_t e = hipMalloc((void**)&c->d_sig2, sig2.size() * sizeof(double));
         if (e != hipSuccess) return fail(c, PHX_ERR_NOMEM, "sigma table: %s", hipGetErrorString(e));
@@ -832,6 +841,8 @@ phx_status phx_load_reflectance(phx_ctx c, const float* r, int32_t n_coat, int32
     const size_t n = (size_t)n_coat * n_s * n_lam;
     std::vector<float> t(n);
     if (set_device(c) != PHX_OK) return PHX_ERR_HIP;
+    const phx_status w = order_wait(c);
+    if (w != PHX_OK) return w;
     hipError_t e = hipMemcpy(t.data(), c->d_coat, n * sizeof(float), hipMemcpyDeviceToHost);
     if (e != hipSuccess) return hip_fail(c, e, "hipMemcpy(coatings)");
     for (size_t i = 0; i < n; ++i)
@@ -887,6 +898,8 @@ phx_status phx_load_screens(phx_ctx c, const phx_atmosphere* a, const float* opd
                                          hipGetErrorString(e));
         c->grad_elems = (size_t)want;
     }
+    const phx_status w = order_wait(c);
+    if (w != PHX_OK) return w;
     const int planes = a->n_layers * a->n_scales;
     unsigned int* d_gmax = nullptr;
     hipError_t e = hipMalloc((void**)&d_gmax, planes * sizeof(unsigned int));

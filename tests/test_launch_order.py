@@ -11,6 +11,7 @@ import pytest
 from paper_1504_06570_amd import phx
 from paper_1504_06570_amd.scene import coatings
 from paper_1504_06570_amd.scene import configs
+from paper_1504_06570_amd.scene.physics import tma_extras
 from paper_1504_06570_amd.scene.readout import Readout
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -51,6 +52,19 @@ class Recorded:
         self.scene.sources.n_photons[:] = 1000
         self.check(self.L.phx_load_sources(self.ctx, phx.sources_struct(self.scene.sources), 3, None,
                                            None, 0, 0))
+
+    def load_reflectance(self):
+        t = np.zeros_like(self.scene.coatings, np.float32)
+        self.check(self.L.phx_load_reflectance(self.ctx, t.ctypes.data, *t.shape))
+
+    def load_physics(self):
+        self.check(self.L.phx_load_physics(self.ctx, C.byref(phx.physics_struct(tma_extras()))))
+
+    def load_screens(self):
+        a = phx.Atmosphere()
+        a.n_layers, a.n_scales, a.screen_n, a.lambda_ref = 1, 1, 4, 500e-9
+        a.height[0], a.pixel[0] = 1000.0, 1.0
+        self.check(self.L.phx_load_screens(self.ctx, C.byref(a), self.memory.ctypes.data, 16, None))
 
     def perturb(self):
         th = (C.c_double * phx.N_THETA)(*([1e-5] * phx.N_THETA))
@@ -144,3 +158,12 @@ def test_the_call_without_allocation_makes_nothing(rec):
     before = rec.L.rec_resources()
     rec.call("trace_noalloc", 0x11, 100000)
     assert rec.L.rec_resources() == before and rec.overlaps() == ""
+
+
+@pytest.mark.parametrize("load", ["reflectance", "physics", "screens", "prescription", "sources"])
+def test_loads_wait_for_the_launch_that_reads_what_they_overwrite(rec, load):
+    getattr(rec, "load_" + load)()
+    rec.call("trace", 0x11)
+    getattr(rec, "load_" + load)()          # tables of the same size
+    rec.call("trace", 0x22)
+    assert rec.overlaps() == ""
