@@ -151,10 +151,10 @@ __global__ __launch_bounds__(kRoBlock) void ro_bleed(const ReadoutJob J, int lds
 }
 
 // Normal deviates in 32 bits, for decisions that are taken again in 64 where they lie within kGaussErr
-// of a boundary (in units of the deviate): log u from the hardware's log2 below one half and
+// of a boundary (in units of the deviate; over every word the radius is within 5.8e-7, sine and cosine
+// within 1.2e-7, and the deviate, the radius being at most 6.8, within 1.8e-6): log u from the hardware's log2 below one half and
 // from 1 - u (exact in whole numbers) above it, by 2 artanh(t / (2 - t)) to the 13th power; sine and cosine
-// of the angle reduced in whole numbers to an eighth of a turn, by their series.  Relative errors of
-// 4e-7 (radius, at most 6.8) and 3e-7 give 5e-6 at most.
+// of the angle reduced in whole numbers to an eighth of a turn, by their series.
 constexpr double kGaussErr = 2e-5;
 struct Polar {
     float r, c, s;
@@ -508,8 +508,9 @@ __global__ __launch_bounds__(kRoBlock) void ro_digitise(const ReadoutJob J) {
     const double rn = J.p.read_noise[amp], gain = J.p.gain[amp], bias = J.p.bias[amp];
     const double nl = J.p.nonlinearity / J.p.full_well;
     // error of the electrons, and of the value by its slope (at most 1 / (gain 0.89^2) where the
-    // linearity term is at least 0.9 and its own error small)
-    const double de = rn * kGaussErr, dv = 1.3 * de / gain + 1e-9;
+    // linearity term is at least 0.9 and its own error small), and the roundings of both forms of the
+    // quotient (twelve of 2^-53 of a quotient that is at most 65536 + |bias| for a value in range)
+    const double de = rn * kGaussErr, dv = 1.3 * de / gain + 2e-15 * (1e6 + fabs(bias));
     const bool bounded = nl * de < 0.01;
     uint32_t noisy = 0;
     for (int b = 0; b < 16; ++b) noisy |= J.p.bit_sigma[b] > 0.0 ? 1u << b : 0u;

@@ -140,3 +140,31 @@ def test_readout_at_the_edges_of_its_kernels(phx, shape, over):
     img[:2, 8:24] = edge
     g, o = run_both(phx, img, rp)
     assert check(g, o) <= 2
+
+
+def test_digitised_values_of_large_cancelling_terms(phx):
+    """Gains so small and biases so large that the two forms of the quotient, e / (g (1 + a e / W)) and
+    e / (g (1 + (a / W) e)), differ by more than any fixed margin: per amplifier the bias puts the
+    first form's value on a whole number that the second form's misses from below."""
+    n_amp, W, a = 16, 1e5, 0.01
+    rng = np.random.default_rng(0)
+    img = np.zeros((64, 128), np.uint32)
+    gain, bias, want = [], [], []
+    while len(gain) < n_amp:
+        ne, g = float(rng.integers(1000, 90000)), 10.0 ** rng.uniform(-9, -5)
+        q1, q2 = ne / (g * (1.0 + a * ne / W)), ne / (g * (1.0 + (a / W) * ne))
+        k = float(rng.integers(100, 60000))
+        b = k - q1
+        if q2 + b < k == q1 + b:
+            amp = len(gain)
+            img[32 * (amp // 8):, 16 * (amp % 8):16 * (amp % 8) + 16] = int(ne)
+            gain.append(g)
+            bias.append(b)
+            want.append(int(k))
+    rp = Readout(amp_nx=8, amp_ny=2, over_x=0, over_y=0, hot_fraction=0.0, dead_fraction=0.0,
+                 hot_column_fraction=0.0, cte_parallel=1.0, cte_serial=1.0, dark_rate=0.0,
+                 full_well=W, nonlinearity=a, gain=tuple(gain + [1.0] * 16),
+                 bias=tuple(bias + [0.0] * 16), read_noise=(0.0,) * 32, bit_sigma=(0.0,) * 16)
+    g, o = run_both(phx, img, rp)
+    assert np.array_equal(o[0], np.array(want, np.uint16)[:, None, None] + np.zeros_like(o[0]))
+    assert np.array_equal(g[0].view(np.uint16), o[0])
