@@ -377,31 +377,32 @@ __device__ __forceinline__ uint32_t packet_electrons(const ReadoutJob& J, uint64
     return STAGE == 3 ? J.work[i] : J.par[i];
 }
 
-// One thread per packet, kPerBlock packets per workgroup; packets above kHeavy electrons go to the heavy
-// list instead, a workgroup's together: one atomic on the list's length each (one per packet
+// One thread per packet, `per` packets per workgroup (light_packets); packets above kHeavy electrons go to
+// the heavy list instead, a workgroup's together: one atomic on the list's length each (one per packet
 // serialised the kernel: 1.4e4 of them 0.46 ms, now 0.11).
 constexpr uint32_t kPerBlock = 4096;
 
 template <int STAGE>
 __global__ __launch_bounds__(kRoBlock) void ro_transfer_light(const ReadoutJob J, uint64_t n,
-                                                              double eps) {
+                                                              uint32_t per, double eps) {
     __shared__ uint16_t s_list[kPerBlock];
     __shared__ uint32_t s_n, s_base;
     uint32_t* count = J.heavy_count + (STAGE - 3);
-    for (uint64_t i0 = (uint64_t)blockIdx.x * kPerBlock; i0 < n;
-         i0 += (uint64_t)gridDim.x * kPerBlock) {   // workgroup-uniform
+    for (uint64_t i0 = (uint64_t)blockIdx.x * per; i0 < n;
+         i0 += (uint64_t)gridDim.x * per) {   // workgroup-uniform
         if (threadIdx.x == 0) s_n = 0;
         __syncthreads();
         constexpr int kBatch = 8;
-        for (uint32_t c = 0; c < kPerBlock; c += kBatch * kRoBlock) {
+        for (uint32_t c = 0; c < per; c += kBatch * kRoBlock) {
+            const int batch = (int)min((uint32_t)kBatch, (per - c) / kRoBlock);
             uint32_t e[kBatch];
 #pragma unroll
             for (int j = 0; j < kBatch; ++j) {
                 const uint64_t i = i0 + c + j * kRoBlock + threadIdx.x;
-                e[j] = i < n ? packet_electrons<STAGE>(J, i) : 0u;
+                e[j] = j < batch && i < n ? packet_electrons<STAGE>(J, i) : 0u;
             }
 #pragma unroll 1
-            for (int j = 0; j < kBatch; ++j) {
+            for (int j = 0; j < batch; ++j) {
                 uint32_t ne = e[0];
 #pragma unroll
                 for (int q = 0; q + 1 < kBatch; ++q) e[q] = e[q + 1];
@@ -576,14 +577,24 @@ hipError_t launch_readout(const ReadoutJob& J, hipStream_t s) {
                            dim3(kRoBlock), 0, s, J);
     const double ep = 1.0 - J.p.cte_parallel, es = 1.0 - J.p.cte_serial;
     const unsigned heavy_grid = 2048;
-    const auto light_grid = [](uint64_t n) {
-        const uint64_t g = (n + kPerBlock - 1) / kPerBlock;
+    // Packets per workgroup: about sixteen workgroups per compute unit, of 256 to 4096 packets (more
+    // workgroups are more appends to the heavy list).  With 4096 everywhere one workgroup held all of 64 x 64
+    // pixels, 16 rounds of packets one after the other: with 30 electrons each 222 us, now 123; 1024 x 1024
+    // of them 268 us, now 200; at 4096 x 4096 the rule gives the 4096.
+    const auto light_packets = [](uint64_t n) {
+        const uint64_t p = (n / 4096 + kRoBlock - 1) / kRoBlock * kRoBlock;
+        return (uint32_t)(p < kRoBlock ? kRoBlock : p > kPerBlock ? kPerBlock : p);
+    };
+    const auto light_grid = [&](uint64_t n) {
+        const uint64_t per = light_packets(n), g = (n + per - 1) / per;
         return dim3((unsigned)(g < (1ull << 20) ? g : 1ull << 20));
     };
     hipLaunchKernelGGL(ro_init, dim3(4096), dim3(kRoBlock), 0, s, J, n_par, n_ser, ep, es);
-    hipLaunchKernelGGL(ro_transfer_light<3>, light_grid(npix), dim3(kRoBlock), 0, s, J, npix, ep);
+    hipLaunchKernelGGL(ro_transfer_light<3>, light_grid(npix), dim3(kRoBlock), 0, s, J, npix,
+                       light_packets(npix), ep);
     hipLaunchKernelGGL(ro_transfer_heavy<3>, dim3(heavy_grid), dim3(kRoBlock), 0, s, J, ep);
-    hipLaunchKernelGGL(ro_transfer_light<4>, light_grid(n_par), dim3(kRoBlock), 0, s, J, n_par, es);
+    hipLaunchKernelGGL(ro_transfer_light<4>, light_grid(n_par), dim3(kRoBlock), 0, s, J, n_par,
+                       light_packets(n_par), es);
     hipLaunchKernelGGL(ro_transfer_heavy<4>, dim3(heavy_grid), dim3(kRoBlock), 0, s, J, es);
     hipLaunchKernelGGL(ro_digitise, dim3(grid_for((uint64_t)ph * pw), (unsigned)n_amp),
                        dim3(kRoBlock), 0, s, J);

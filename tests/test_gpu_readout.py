@@ -168,3 +168,44 @@ def test_digitised_values_of_large_cancelling_terms(phx):
     g, o = run_both(phx, img, rp)
     assert np.array_equal(o[0], np.array(want, np.uint16)[:, None, None] + np.zeros_like(o[0]))
     assert np.array_equal(g[0].view(np.uint16), o[0])
+
+
+@pytest.mark.parametrize("shape", [(1024, 1024), (1024, 1028), (2056, 4096)])
+def test_readout_where_the_packets_per_workgroup_change(phx, shape):
+    """256 packets per workgroup, 512, and a part of a second batch of loads (2304): sparse spots at the
+    limits of the transfers on an empty image, stage by stage against the oracle."""
+    rng = np.random.default_rng(4)
+    img = np.zeros(shape, np.uint32)
+    n = 3000
+    img[rng.integers(0, shape[0], n), rng.integers(0, shape[1], n)] = rng.choice(
+        [1, 4, 63, 64, 65, 257, 3000], n)
+    rp = Readout(amp_nx=4, amp_ny=2, dark_rate=0.0, hot_column_fraction=0.0, cte_parallel=1 - 1e-5,
+                 cte_serial=1 - 1e-5)
+    g, o = run_both(phx, img, rp)
+    assert check(g, o) <= 2
+
+
+def _time(phx, images):
+    """Median seconds of a readout of each image, taken in turn."""
+    import time
+    import torch
+    tr = phx.Tracer(C.tiny(scale=1e-4))
+    dev = [torch.from_numpy(i.astype(np.int32)).cuda() for i in images]
+    rp = Readout(amp_nx=4, amp_ny=2)
+    t = [[] for _ in dev]
+    for k in range(25):
+        for j, d in enumerate(dev):
+            torch.cuda.synchronize()
+            a = time.perf_counter()
+            tr.readout(d, rp)
+            torch.cuda.synchronize()
+            t[j].append(time.perf_counter() - a)
+    tr.close()
+    return [float(np.median(v[5:])) for v in t]
+
+
+def test_a_small_image_is_spread_over_the_compute_units(phx):
+    """64 x 64 pixels: their electrons cost little beside the launches (1.9 times an empty image's time
+    when one workgroup held them all, 1.1 now)."""
+    empty, full = _time(phx, [np.zeros((64, 64)), np.full((64, 64), 60)])
+    assert full < 1.5 * empty
