@@ -344,9 +344,30 @@ __device__ __forceinline__ Kept ro_transfer(const Packet& k, uint64_t idx, doubl
     return Kept{words - late, late - longer};
 }
 
-// A packet with more electrons than this is handed to whole wavefronts (the heavy list): in
-// the other kernel it would hold up the 63 packets beside it.
-constexpr uint32_t kHeavy = 64;
+// Packets with more electrons than some limit are handed to whole wavefronts (the heavy list): in the
+// other kernel one of them holds up the 63 packets beside it, for one block of draws per four electrons.
+// A wavefront weighs the two (light_limit): a limit t costs it up to (t - kHeavy) / 4 blocks more, a
+// packet above the limit about kHeavyBlocks of them in the other kernel (0.97 ns a packet against 0.09 ns a
+// wavefront's block on the filled chip).  So a bright pixel among dark ones goes to the list, and a
+// background, with which all packets of the wavefront are as large, does not.  4096 x 4096 pixels of 300
+// electrons take 5.7 ms (with every packet above 64 on the list 41.8; with up to 1024 never on it 8.7), of
+// 1000 26 (53.7; 44.5); a field of 1e4 stars without a background 2.6 either way (4.5), at 1024 x 1024
+// 0.33 (0.34; 0.72).  4 and 12 blocks gave the same within 3 % but for 1000 (4: 54 ms) and 2000 electrons
+// (12: 34 ms, against 65) and the small dense field (12: 0.344 against 0.331).
+constexpr uint32_t kHeavy = 64, kLightMax = 2048, kHeavyBlocks = 8;
+
+__device__ __forceinline__ uint32_t light_limit(uint32_t ne) {
+    uint32_t cost = kHeavyBlocks * (uint32_t)__popcll(__ballot(ne > kHeavy)), lim = kHeavy;
+    if (cost == 0) return lim;   // the wavefront's
+    for (uint32_t t = 2 * kHeavy; t <= kLightMax; t *= 2) {
+        const uint32_t c = (t - kHeavy) / 4 + kHeavyBlocks * (uint32_t)__popcll(__ballot(ne > t));
+        if (c < cost) {
+            cost = c;
+            lim = t;
+        }
+    }
+    return lim;
+}
 
 __device__ __forceinline__ uint64_t div_by(uint64_t a, uint64_t b) {
     return (a | b) >> 32 ? a / b : (uint64_t)((uint32_t)a / (uint32_t)b);
@@ -377,8 +398,8 @@ __device__ __forceinline__ uint32_t packet_electrons(const ReadoutJob& J, uint64
     return STAGE == 3 ? J.work[i] : J.par[i];
 }
 
-// One thread per packet, `per` packets per workgroup (light_packets); packets above kHeavy electrons go to
-// the heavy list instead, a workgroup's together: one atomic on the list's length each (one per packet
+// One thread per packet, `per` packets per workgroup (light_packets); packets above the wavefront's limit go
+// to the heavy list instead, a workgroup's together: one atomic on the list's length each (one per packet
 // serialised the kernel: 1.4e4 of them 0.46 ms, now 0.11).
 constexpr uint32_t kPerBlock = 4096;
 
@@ -406,9 +427,10 @@ __global__ __launch_bounds__(kRoBlock) void ro_transfer_light(const ReadoutJob J
                 uint32_t ne = e[0];
 #pragma unroll
                 for (int q = 0; q + 1 < kBatch; ++q) e[q] = e[q + 1];
+                const uint32_t lim = light_limit(ne);   // of every lane of the wavefront
                 if (ne == 0) continue;
                 const uint32_t o = c + j * kRoBlock + threadIdx.x;
-                if (ne > kHeavy && eps > 0.0) {
+                if (ne > lim && eps > 0.0) {
                     s_list[atomicAdd(&s_n, 1u)] = (uint16_t)o;
                     continue;
                 }

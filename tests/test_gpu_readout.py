@@ -209,3 +209,30 @@ def test_a_small_image_is_spread_over_the_compute_units(phx):
     when one workgroup held them all, 1.1 now)."""
     empty, full = _time(phx, [np.zeros((64, 64)), np.full((64, 64), 60)])
     assert full < 1.5 * empty
+
+
+def test_a_background_is_not_handed_out_packet_by_packet(phx):
+    """Pixels that all hold 300 electrons: 2.4 times the time of 10 (11.5 when every packet above 64 was
+    handed to whole wavefronts)."""
+    rng = np.random.default_rng(6)
+    dark, bright = _time(phx, [rng.poisson(10.0, (1024, 1024)), rng.poisson(300.0, (1024, 1024))])
+    assert bright < 5.0 * dark
+
+
+@pytest.mark.parametrize("shape,layout", [((128, 256), (4, 2)), ((3, 130), (1, 1))])
+def test_readout_at_the_limits_a_wavefront_chooses(phx, shape, layout):
+    """Wavefronts with 0 to 64 packets at and beside each limit between the two transfer kernels (64 to
+    2048 electrons by doubling), alone and among others above it: every stage against the oracle."""
+    rng = np.random.default_rng(8)
+    edges = np.array([63, 64, 65, 127, 128, 129, 256, 257, 512, 513, 1024, 1025, 2047, 2048, 2049,
+                      5000])
+    img = rng.poisson(20.0, shape).astype(np.uint32)
+    flat = img.reshape(-1)
+    for w in range(flat.size // 64):
+        k = int(rng.integers(0, 65))
+        at = 64 * w + rng.permutation(64)[:k]
+        flat[at] = rng.choice(edges[:int(rng.integers(1, edges.size + 1))], k)
+    rp = Readout(amp_nx=layout[0], amp_ny=layout[1], dark_rate=0.0, cte_parallel=1 - 1e-4,
+                 cte_serial=1 - 5e-5)
+    g, o = run_both(phx, img, rp)
+    assert check(g, o) <= 2
