@@ -286,10 +286,14 @@ constexpr int kTileIters = 8;
 constexpr uint32_t kFrontExtra = PHX_F_DISPERSION | PHX_F_DOME | PHX_F_HALO | PHX_F_SECOND_KICK;
 constexpr uint32_t kBackExtra = PHX_F_AEROSOL | PHX_F_SPIDER | PHX_F_GHOSTS;
 
-// Ghost list: a wavefront of the sequential pass reserves kGhostReserve entries at a time (at least 64), one
-// of the branch pass claims kGhostClaim.  The list holds an entry for each photon of a chunk and the
-// entries that the wavefronts leave unused.
-constexpr uint64_t kGhostReserve = 128, kGhostClaim = 64;
+// Ghost list: a wavefront of the sequential pass with at least kGhostUnits units to trace reserves
+// kGhostReserve entries at a time (at least 64), one with fewer the entries that it appends; a
+// wavefront of the branch pass takes kGhostClaim at a time, in turn while the list holds at most
+// kGhostDealt of them per wavefront, else from a counter (an atomic on one address takes 25 ns, and each of
+// the wavefronts needs one to find the list empty: 1e4 photons 395 us with the counter, 229 in
+// turn; 3e7 9.8 ms with it, 10.3 in turn, where the branches' lengths balance).  The list holds an entry
+// for each photon of a chunk and the entries that the wavefronts leave unused.
+constexpr uint64_t kGhostReserve = 128, kGhostUnits = 4, kGhostClaim = 64, kGhostDealt = 4;
 constexpr uint64_t ghost_entries(uint64_t chunk, int n_cu, int back_per_cu) {
     const uint64_t launched = (uint64_t)n_cu * kGroupsPerUnit * back_per_cu * (kThreads / 64);
     const uint64_t filled = chunk / 64 + kThreads / 64;   // no more workgroups than units of work

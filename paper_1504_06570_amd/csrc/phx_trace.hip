@@ -1122,12 +1122,16 @@ __device__ __forceinline__ void ghost_stage(GhostSink* gs, const Hit& h, int k, 
     gs->g[3 * 64] = n_cur;
     gs->k = k;
 }
-// Appends the lanes holding a ghost start (gs.k >= 0) to the list.  A wavefront reserves
-// kGhostReserve entries at a time (ctr[0] counts the reserved ones; an entry beyond cap, which the
+// Appends the lanes holding a ghost start (gs.k >= 0) to the list.  A wavefront with many units ahead
+// of it reserves kGhostReserve entries at a time (ctr[0] counts the reserved ones; an entry beyond cap, which the
 // list's size rules out, is not written): an atomic for each append, all on one address, held the pass
-// up (2.6e7 photons 2.9 ms, now 2.35; the unused entries cost the branch pass 0.3 of its 4.7).  Every lane of the wavefront must call it.
+// up (2.6e7 photons 2.9 ms, now 2.35; the unused entries cost the branch pass 0.3 of its 4.7).  One with few
+// reserves what it appends (`reserve` 0): most of its block would stay unused, and the branch pass would
+// start a wavefront for each (3e5 photons without the pre-roll 534 us, now 372; the line at 2, 4, 8 units:
+// 2e6 photons with the pre-roll 1.27, 1.22, 1.22 ms, 4e6 without 2.33, 2.33, 2.46).  Every lane of the wavefront must call it.
 struct GhostRoom {
     uint64_t next, end;   // the wavefront's reserved, not yet written entries
+    uint64_t reserve;     // entries to reserve at a time, at least
 };
 __device__ __forceinline__ void ghost_append(double* q, uint64_t cap, unsigned long long* ctr,
                                              GhostRoom& room, const GhostSink& gs, const Outcome& o,
@@ -1139,12 +1143,13 @@ __device__ __forceinline__ void ghost_append(double* q, uint64_t cap, unsigned l
     const uint64_t rank = (uint64_t)__popcll(pm & ((1ull << __lane_id()) - 1ull));
     uint64_t e = room.next + rank;
     if (n > avail) {
+        const uint64_t more = max(n - avail, room.reserve);
         unsigned long long b = 0;
-        if (__lane_id() == 0) b = atomicAdd(&ctr[0], (unsigned long long)kGhostReserve);
+        if (__lane_id() == 0) b = atomicAdd(&ctr[0], (unsigned long long)more);
         b = __shfl(b, 0);
         if (rank >= avail) e = b + (rank - avail);
         room.next = b + (n - avail);
-        room.end = b + kGhostReserve;
+        room.end = b + more;
     } else {
         room.next += n;
     }
@@ -2151,8 +2156,8 @@ constexpr int kWaves = kBlock / 64;
 // EXTRA: aerosol and the spider at the entrance.  GH, the ghost branch of the roulette (with
 // ghosts the kernel runs twice per chunk): 0 none; 1 the sequential pass, which appends the
 // photons a coating reflects to the chunk's ghost list (ghost_list, cap entries, ghost_ctr[0]
-// their number) instead of booking them; 2 the branches of the listed photons, claimed
-// kGhostClaim at a time through ghost_ctr[1], with every lane refilled from the claimed entries as its photon is
+// their number) instead of booking them; 2 the branches of the listed photons, taken
+// kGhostClaim at a time (ghost_ctr[1] counts the claimed ones), with every lane refilled from them as its photon is
 // settled.  Keeping the branches out of the sequential pass keeps its registers those of the
 // kernel without ghosts.
 // Four wavefronts per SIMD (128 VGPRs; without the compiler's hoisting of constants out of the loop the
@@ -2199,11 +2204,14 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) 
     int qn = 0;                                // queued photons (wavefront-uniform)
     uint32_t newton = 0, traced = 0;
     if (GH == 2) {
-        // the branches: the wavefront claims kGhostClaim listed starts at a time; a lane whose photon is
+        // the branches: the wavefront takes kGhostClaim listed starts at a time; a lane whose photon is
         // settled takes the next claimed start, so that the lanes stay busy until the list is
         // exhausted
         const uint64_t total = min((uint64_t)ghost_ctr[0], ghost_cap);
         uint64_t wbase = 0, wend = 0;   // the wavefront's claimed, not yet started entries
+        // a list of a few claims per wavefront is dealt out in turn
+        const bool dealt = total <= kGhostDealt * n_waves * kGhostClaim;
+        uint64_t next = ((uint64_t)blockIdx.x * kWaves + wave) * kGhostClaim;
         bool claims = true;
         bool busy = false;
         GhostRay gr;
@@ -2216,9 +2224,13 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) 
         for (;;) {
             const uint64_t idle = __ballot(!busy);
             if (claims && idle && wbase == wend) {
-                unsigned long long b = 0;
-                if (lane == 0) b = atomicAdd(&ghost_ctr[1], (unsigned long long)kGhostClaim);
-                b = __shfl(b, 0);
+                unsigned long long b = next;
+                if (dealt) {
+                    next += n_waves * kGhostClaim;
+                } else {
+                    if (lane == 0) b = atomicAdd(&ghost_ctr[1], (unsigned long long)kGhostClaim);
+                    b = __shfl(b, 0);
+                }
                 wbase = b < total ? b : total;
                 wend = b + kGhostClaim < total ? b + kGhostClaim : total;
                 claims = wbase < wend;
@@ -2257,7 +2269,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) 
             book(P, L, fin, g, si, idx, o, s_stats, s_win, kWin, &s_org, &s_mc);
         }
     }
-    GhostRoom room{0, 0};
+    GhostRoom room{0, 0, n_units >= kGhostUnits * n_waves ? kGhostReserve : 0};
     for (;;) {
         if (GH == 2) break;
         const bool more = unit < n_units;
@@ -3094,7 +3106,11 @@ hipError_t launch_trace(const DevParams* dparams, const Launch& L, const Workspa
             hipLaunchKernelGGL(k1, bg, dim3(kBlock), 0, bs, dparams, L, sp.begin, S.surv(c),
                                S.cnt(c), sp.len, (const double*)S.state_buf(c), W.chunk, bt,
                                W.ghost_list, W.ghost_cap, W.ghost_ctr);
-            hipLaunchKernelGGL(k2, dim3((unsigned)bcap), dim3(kBlock), 0, bs, dparams, L,
+            const uint64_t claims = (ghost_entries(sp.len, n_cu, cfg.back_per_cu) + kGhostClaim - 1) /
+                                    kGhostClaim;
+            const dim3 gg = grid_of((claims + kWaves - 1) / kWaves, n_cu,
+                                    kGroupsPerUnit * cfg.back_per_cu);
+            hipLaunchKernelGGL(k2, gg, dim3(kBlock), 0, bs, dparams, L,
                                sp.begin, S.surv(c), S.cnt(c), sp.len,
                                (const double*)S.state_buf(c), W.chunk,
                                (unsigned long long*)nullptr, W.ghost_list, W.ghost_cap,

@@ -97,3 +97,51 @@ def test_lists_of_many_sources_without_an_atmosphere(phx):
     torch.cuda.synchronize()
     assert torch.equal(img, ref) and torch.equal(m, mr)
     tr.close()
+
+
+def _ghosts(phx):
+    from paper_1504_06570_amd.scene import coatings as cm
+    from paper_1504_06570_amd.scene import configs as C
+    scene = C.full(scale=1e-6, screen_n=64)
+    scene.reflectance = cm.standard_reflectance()
+    return phx.Tracer(scene), int(scene.physics) | phx.F_GHOSTS
+
+
+@pytest.mark.parametrize("photons,shape", [
+    (1, {}), (65, {}), (1000003, dict(back_blocks_per_cu=1)),   # blocks of the list reserved, or not
+    (20000003, dict(chunk_log2=18)),                            # branches claimed, or dealt out
+    (20000003, dict(chunk_log2=20, dynamic_tiles=1)),
+])
+def test_ghost_lists_of_every_size_hold_the_same_starts(phx, photons, shape):
+    """The ghost list reserved by blocks and entry by entry, its branches from a counter and in turn:
+    the same image, and every photon in one place of the statistics."""
+    import torch
+    tr, flags = _ghosts(phx)
+    want, st, _, _ = tr.trace(flags=flags, stats=tr.new_stats(), photon_count=photons)
+    tr.set_launch_config(**shape)
+    got, st2, _, _ = tr.trace(flags=flags, stats=tr.new_stats(), photon_count=photons)
+    torch.cuda.synchronize()
+    assert torch.equal(got, want) and torch.equal(st, st2)
+    assert int(phx.stats_table(st).sum()) == photons
+    tr.close()
+
+
+def test_a_short_ghost_list_takes_few_wavefronts(phx):
+    """1e4 photons: the branch pass is launched for the entries there can be, however wide the launch
+    shape is (a counter's atomic for each wavefront of the widest took 20 times the rest)."""
+    import time
+    import torch
+    tr, flags = _ghosts(phx)
+    img, t = tr.new_image(), {}
+    for width in (2, 64):
+        tr.set_launch_config(back_blocks_per_cu=width)
+        v = []
+        for _ in range(15):
+            torch.cuda.synchronize()
+            a = time.perf_counter()
+            tr.trace(img, flags=flags, photon_count=10000)
+            torch.cuda.synchronize()
+            v.append(time.perf_counter() - a)
+        t[width] = float(np.median(v[5:]))
+    tr.close()
+    assert t[64] < 3.0 * t[2], t
