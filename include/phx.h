@@ -423,8 +423,9 @@ phx_status phx_trace_noalloc(phx_ctx ctx, const phx_trace_args* args, void* stre
 /* Launch shape of phx_trace / phx_trace_batched / phx_adjoint.  chunk_log2: photons per chunk =
  * 2^chunk_log2 (16..27; the context keeps lists and 48-byte states for two chunks);
  * generate_blocks_per_cu: workgroups of 256 lanes per compute unit for the pre-roll;
- * front_, back_blocks_per_cu: the same in fours for the sky+atmosphere and optics kernels
- * (each 1..64); dynamic_tiles: 0 = static grid-stride, 1 = the sky kernel claims tiles of
+ * front_, back_blocks_per_cu: the same for the sky+atmosphere and optics kernels, in fours with the
+ * static schedule, so that a setting of n launches 4 n of them, of which four (optics) to seven are
+ * resident (each setting 1..64); dynamic_tiles: 0 = static grid-stride, 1 = the sky kernel claims tiles of
  * 2048 photons and each optics wavefront units of 64 from device counters; pipeline: 1 = each
  * chunk's pre-roll and optics stages run on a context-owned second stream, overlapping
  * the sort and sky stage of the next chunk on the caller's stream (ordered by

@@ -264,15 +264,10 @@ struct Pipe {
     hipEvent_t* ev = nullptr;    // at least 3 n_chunks + 1 events
     uint64_t n_ev = 0;
 };
-// Launch shape (tunable): workgroups of the pre-roll per compute unit, groups of four workgroups (one
-// for each SIMD's wavefronts) of the sky and optics stages, and the schedule of the
+// Launch shape (tunable): workgroups of the pre-roll per compute unit, workgroups of the sky and optics
+// stages (in fours for the static schedule: stage_groups), and the schedule of the
 // sky and optics stages (static grid-stride, or tiles of kTileIters x 256 photons taken from a
 // device counter).
-// By default the optics stage then is queued twice as deep as it is resident (4 workgroups per compute
-// unit) and the sky stage holds about one tile per workgroup, so that compute units which finish
-// early, or share theirs with the other stage, take fewer of them: 1e9 photons 37.2 ms with 4 and 48
-// workgroups, 35.5 with 8 and 192; 3e7 without the pre-roll 7.8 and 7.1.
-constexpr int kGroupsPerUnit = 4;
 struct LaunchConfig {
     int generate_per_cu = 16;
     int front_per_cu = 48;
@@ -281,6 +276,18 @@ struct LaunchConfig {
     int pipeline = 1;
 };
 constexpr int kTileIters = 8;
+// Workgroups of the sky or optics stage per compute unit.  The static schedule takes the setting in fours: by
+// default the optics stage then is queued twice as deep as it is resident (4 workgroups per compute
+// unit) and the sky stage holds about one tile per workgroup, so that compute units which finish
+// early, or share theirs with the other stage, take fewer of them: 1e9 photons 37.2 ms with 4 and 48
+// workgroups, 35.5 with 8 and 192; 3e7 without the pre-roll 7.8 and 7.1.  The dynamic schedule takes it as
+// it is: its wavefronts balance by their claims, and each workgroup more is an atomic more on the one
+// counter, to find the work done (1e6 photons 0.38 ms with fours, 0.32 without; 1e8 on two streams 6.98 and
+// 5.55).
+constexpr int kGroupsPerUnit = 4;
+constexpr int stage_groups(const LaunchConfig& cfg, int per_cu) {
+    return cfg.dynamic ? per_cu : kGroupsPerUnit * per_cu;
+}
 // Flags that select the sky and optics kernels carrying the per-photon physics beyond the core
 // path (the other instantiations hold none of its code).
 constexpr uint32_t kFrontExtra = PHX_F_DISPERSION | PHX_F_DOME | PHX_F_HALO | PHX_F_SECOND_KICK;
@@ -295,7 +302,7 @@ constexpr uint32_t kBackExtra = PHX_F_AEROSOL | PHX_F_SPIDER | PHX_F_GHOSTS;
 // for each photon of a chunk and the entries that the wavefronts leave unused.
 constexpr uint64_t kGhostReserve = 128, kGhostUnits = 4, kGhostClaim = 64, kGhostDealt = 4;
 constexpr uint64_t ghost_entries(uint64_t chunk, int n_cu, int back_per_cu) {
-    const uint64_t launched = (uint64_t)n_cu * kGroupsPerUnit * back_per_cu * (kThreads / 64);
+    const uint64_t launched = (uint64_t)n_cu * kGroupsPerUnit * back_per_cu * (kThreads / 64);   // at most
     const uint64_t filled = chunk / 64 + kThreads / 64;   // no more workgroups than units of work
     return chunk + kGhostReserve * (launched < filled ? launched : filled);
 }

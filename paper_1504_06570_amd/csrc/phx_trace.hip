@@ -2994,7 +2994,8 @@ struct Stages {
             sort_photons(W, sp, c, seg_buf(c), seg_n_buf(c), surv_buf(c), stable, stream);
             mark(3, 1, stream);
         }
-        const dim3 fg = grid_of((sp.len + kBlock - 1) / kBlock, n_cu, kGroupsPerUnit * cfg.front_per_cu);
+        const dim3 fg = grid_of((sp.len + kBlock - 1) / kBlock, n_cu,
+                                stage_groups(cfg, cfg.front_per_cu));
         // the dies take a pupil sector each (a grid that covers them evenly, the static schedule)
         const uint32_t* sect = sorted(c) && (L.flags & PHX_F_ATMOSPHERE) && !ft &&
                                        fg.x % kSectors == 0 ? W.sect + 16 * c : nullptr;
@@ -3091,7 +3092,7 @@ hipError_t launch_trace(const DevParams* dparams, const Launch& L, const Workspa
     S.run(n_chunks, cfg.dynamic != 0, [&](uint64_t c, hipStream_t bs) {
         const ChunkSpan& sp = W.plan[c];
         const uint64_t want = (sp.len + kBlock - 1) / kBlock;
-        const uint64_t bcap = (uint64_t)n_cu * kGroupsPerUnit * cfg.back_per_cu;
+        const uint64_t bcap = (uint64_t)n_cu * stage_groups(cfg, cfg.back_per_cu);
         const dim3 bg((unsigned)(want < bcap ? want : bcap));
         unsigned long long* bt = cfg.dynamic ? W.tiles + 2 * c + 1 : nullptr;
         S.mark(2, 0, bs);
@@ -3109,7 +3110,7 @@ hipError_t launch_trace(const DevParams* dparams, const Launch& L, const Workspa
             const uint64_t claims = (ghost_entries(sp.len, n_cu, cfg.back_per_cu) + kGhostClaim - 1) /
                                     kGhostClaim;
             const dim3 gg = grid_of((claims + kWaves - 1) / kWaves, n_cu,
-                                    kGroupsPerUnit * cfg.back_per_cu);
+                                    stage_groups(cfg, cfg.back_per_cu));
             hipLaunchKernelGGL(k2, gg, dim3(kBlock), 0, bs, dparams, L,
                                sp.begin, S.surv(c), S.cnt(c), sp.len,
                                (const double*)S.state_buf(c), W.chunk,
