@@ -31,9 +31,9 @@ PMC_SUMMARY = os.path.join(ROOT, "profiles", "trace_kernel_full_1e9_pmc.json")
 PEAK_INT32_TOPS = 78.6    # 32-bit integer VALU lane operations: 256 CU x 4 SIMD x 32 lanes x 2.4 GHz
 OP_COUNTS = os.path.join(ROOT, "profiles", "oracle_op_counts_full.json")
 FP64_FIELDS = ("add", "mul", "div", "sqrt", "trans")
-# Implementation traffic of the sky stage (not the method's): the 7-double start-plane state each
+# Implementation traffic of the sky stage (not the method's): the 6-double start-plane state each
 # traced photon hands to the optics stage.
-STATE_BYTES = 7 * 8
+STATE_BYTES = 6 * 8
 # Integer operations of one Philox4x32-10 block: ten rounds of two 32x32 -> 64-bit products, two
 # three-way XORs (four XORs) and two key additions.
 PHILOX_INT_OPS = 10 * 8
@@ -484,8 +484,8 @@ def ghost_leg(tr, flags, steps, n_ph, core_ms, tune=True):
 
 
 def launch_shape(text):
-    """--launch G,F,B[,C]: pre-roll, sky and optics workgroups per compute unit, and optionally
-    the chunk size's log2."""
+    """--launch G,F,B[,C]: pre-roll, sky and optics workgroups per compute unit (sky and optics in
+    fours), and optionally the chunk size's log2."""
     v = [int(x) for x in text.split(",")]
     if len(v) not in (3, 4):
         raise SystemExit("bench.py: --launch takes G,F,B or G,F,B,C")
@@ -781,7 +781,7 @@ def summarize_pmc(dirs, copy_dirs, photons, json_out):
              f"{write_kib:.0f} KiB WRITE_SIZE for 1 GiB each way -> fetch factor "
              f"{fetch_factor:.3f}, write factor {write_factor:.3f}", ""]
     for k in sorted(kernels, key=lambda k: -hbm.get(k, 0.0)):
-        if not any(t in k for t in ("_kernel", "bucket_", "compact_")):
+        if not any(t in k for t in ("_kernel", "sort_")):
             continue
         lines.append(f"{k}   dispatches {calls[k]}" +
                      (f"   HBM bytes per launch {hbm[k]:.4e}" if k in hbm else ""))
@@ -818,8 +818,8 @@ def main():
                     help="run one secondary leg alone and print its record (for profiling)")
     ap.add_argument("--launch", default=None, metavar="G,F,B[,C]",
                     help="fixed launch shape (pre-roll, sky and optics workgroups per compute "
-                         "unit, optionally the chunk size's log2) in place of the autotuner, so "
-                         "that a profile holds only the timed launches")
+                         "unit, the latter two in fours, optionally the chunk size's log2) in "
+                         "place of the autotuner, so that a profile holds only the timed launches")
     ap.add_argument("--no-single-stream", action="store_true",
                     help="skip the step with both stages on one stream")
     ap.add_argument("--summarize-stats", default=None, metavar="CSV",
@@ -939,7 +939,7 @@ def main():
                                     "launch_ms": v["ms"], "work_per_launch": v["work"]}
     implementation = {
         "front_state_write_bytes_per_launch": traced * STATE_BYTES / chunks,
-        "note": "the sky stage also writes the 7-double start-plane state of each traced photon "
+        "note": "the sky stage also writes the 6-double start-plane state of each traced photon "
                 "for the optics stage; that traffic comes from splitting the trace into kernels "
                 "and is not in the algorithmic bytes",
     }

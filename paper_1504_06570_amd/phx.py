@@ -493,7 +493,9 @@ class Tracer:
         return cfg.as_dict()
 
     def set_launch_config(self, **kw):
-        """Change the launch shape; unspecified fields keep their value."""
+        """Change the launch shape; unspecified fields keep their value.  front_blocks_per_cu and
+        back_blocks_per_cu count workgroups in fours with the static schedule, one by one with
+        dynamic_tiles=1; generate_blocks_per_cu always one by one."""
         cfg = LaunchConfig()
         self._check(self.L.phx_get_launch_config(self.ctx, C.byref(cfg)))
         for k, v in kw.items():

@@ -81,3 +81,19 @@ def test_launch_shape_parses_widths_and_an_optional_chunk_size():
     for bad in ("16,48", "1,2,3,4,5"):
         with pytest.raises(SystemExit):
             bench.launch_shape(bad)
+
+
+def test_summarize_pmc_lists_the_sort_and_counts_the_state_that_is_written(tmp_path):
+    import re
+    rows = [(f"void phx::{k}(int)", "FETCH_SIZE", 1.0)
+            for k in ("generate_kernel<true, false>", "sort_count", "sort_scan", "sort_scatter<false>")]
+    _counters(tmp_path / "f", rows)
+    copy = [("__amd_rocclr_copyBuffer", c, 1048576.0) for c in ("FETCH_SIZE", "WRITE_SIZE")]
+    _counters(tmp_path / "c", copy)
+    table = bench.summarize_pmc([str(tmp_path / "f")], [str(tmp_path / "c")], 1e9,
+                                str(tmp_path / "pmc.json"))
+    for k in ("generate_kernel<true, false>", "sort_count", "sort_scan", "sort_scatter<false>"):
+        assert k in table
+    internal = open(os.path.join(ROOT, "paper_1504_06570_amd", "csrc", "phx_internal.h")).read()
+    fields = int(re.search(r"kStateFields = (\d+);", internal).group(1))
+    assert bench.STATE_BYTES == 8 * fields
