@@ -54,10 +54,10 @@ struct phx_ctx_s {
     int32_t* d_src_guide = nullptr;       // photon-block -> source guide of the prefix table
     size_t src_guide_cap = 0;
     uint32_t guide_shift = 0;
-    uint32_t* d_survivors = nullptr;     // pre-roll survivors of one chunk
-    unsigned int* d_counts = nullptr;    // survivor count per chunk
+    uint32_t* d_survivors = nullptr;     // lists of photons to trace of two chunks
+    unsigned int* d_counts = nullptr;    // their number per chunk
     uint64_t counts_cap = 0;
-    double* d_state = nullptr;           // start-plane state of one chunk [7][ws_chunk]
+    double* d_state = nullptr;           // start-plane states of two chunks [2][kStateFields][ws_chunk]
     uint64_t ws_chunk = 0;
     double* d_ghost = nullptr;           // ghost list of a chunk (with ghosts) and its counters
     uint64_t ghost_cap = 0;
@@ -68,7 +68,7 @@ struct phx_ctx_s {
     std::vector<std::pair<int, std::pair<size_t, size_t>>> ev_pairs;   // kind, (start, stop)
     size_t ev_used = 0;
     long pending_start[4] = {-1, -1, -1, -1};
-    double timing_ms[4] = {0, 0, 0, 0};   // pre-roll bitmap, sky, optics, compaction
+    double timing_ms[4] = {0, 0, 0, 0};   // pre-roll, sky, optics, sort
     double timing_chunks = 0;
     // launch shape, prefix-table cache, captured graphs (phx_trace_batched)
     phx::LaunchConfig cfg;
@@ -1205,9 +1205,13 @@ uint32_t guide_shift_of(uint64_t total, int n_src) {
 
 // How a chunk's photons to trace are listed (sort_scatter and class_kernel say what the orders are
 // for).  The order pays once a chunk holds more photons than are in flight at a time (2.6e5 lanes of
-// the sky kernel): with the pre-roll's 13 % from 2^21 photons on, without it from 2^20 on.  Below,
-// and in phx_trace_noalloc's small chunks, the launches cost more than they save.  An adjoint's pre-roll
-// survivors are always sorted: the order of its sums then is the same on every run.
+// the sky kernel); far below, and in phx_trace_noalloc's small chunks, the sort's launches cost more than
+// they save.  Whole traces, seven layers of 2048 x 2048 cells, sorted / as they come, in us: with the
+// pre-roll 1e5 photons 81 / 77, 1e6 120 / 125, 2e6 184 / 196, 2.2e6 195 / 203, 8e6 491 / 529;
+// without it 6e5 240 / 277, 1e6 391 / 428, 1.1e6 418 / 455, 8e6 2060 / 2884.  The lines, at 2^21 and 2^20,
+// are on the safe side: smaller screens have less to gain, and just below them a few per cent are left.
+// By class alone, without an atmosphere: 6e5 121 / 119, 1e6 162 / 170, 2e6 251 / 244, 4e6 419 / 440.
+// An adjoint's pre-roll survivors are always sorted: the order of its sums then is the same on every run.
 int list_order(const phx_ctx c, const phx_trace_args* a, uint64_t len, bool adjoint, bool noalloc) {
     if (noalloc) return phx::kListAsIs;
     const bool atm = (a->flags & PHX_F_ATMOSPHERE) != 0, coat = (a->flags & PHX_F_COATINGS) != 0;

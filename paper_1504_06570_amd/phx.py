@@ -521,7 +521,8 @@ class Tracer:
 
     def get_timing(self):
         """Accumulated kernel milliseconds since timing was switched on:
-        dict(generate, front, back, chunks, compact)."""
+        dict(generate, front, back, chunks, compact); compact is the sort of the photons to
+        trace."""
         out = (C.c_double * 5)()
         self._check(self.L.phx_get_timing(self.ctx, out, 5))
         return dict(generate=out[0], front=out[1], back=out[2], chunks=out[3], compact=out[4])
