@@ -173,7 +173,7 @@ __device__ __forceinline__ void zernike_poly(const double* c, double u, double v
 // What every passage needs of a surface, read with one scalar load and held in scalar registers.
 // The empty asm keeps the compiler from sinking each field's load to its first use, where the
 // wavefront would wait for it alone: with about ten such waits per surface, 45 % of the optics
-// kernel's wavefront time went into waiting (189 scalar loads per 64 photons; now 93, and 38 %).
+// kernel's wavefront time went into waiting (189 scalar loads per 64 photons; now 99, and 35 %).
 struct SurfRegs {
     uint32_t bits;
     int32_t coating;
@@ -354,8 +354,8 @@ __device__ __forceinline__ Float4 pair_swap(const Float4& v) {
 // record, then of the odd lane's, and exchange them.  Two loads of a lane from one record stall the
 // first-level cache, which waits at the second for the first one's line and with that keeps no more than
 // about one load's 64 lines on their way; a pair's halves are one request.  Sky stage of 2^26
-// photons (8.6e6 traced) 1.48 -> 1.22 ms, 6.1 TB/s of lines from beyond the L2 (seven
-// finest-scale lines per photon, which are of no use to another photon in flight).
+// photons (8.8e6 traced) 1.48 -> 1.22 ms, for 5.6e7 lines from beyond the L2, 5.9 TB/s (six a photon, nearly
+// all of the finest scale, which are of no use to another photon in flight).
 __device__ __forceinline__ void screen_tap(const float4* g, uint32_t N, double side,
                                            double inv_side, double sx, double sy, double inv_pix,
                                            double& ax, double& ay) {
