@@ -413,11 +413,10 @@ phx_status phx_trace(phx_ctx ctx, const phx_trace_args* args, void* stream);
  * the same arguments (the launch is cut into chunks of at most 2^19 photons, run on `stream`
  * alone).  Limits: at most 65536 sources and 16384 chunks (about 8.6e9 photons); PHX_F_GHOSTS
  * is refused (PHX_ERR_INVALID: the ghost list needs context memory); beyond a limit
- * PHX_ERR_CAPACITY, nothing enqueued.  Every call on one GPU shares that GPU's workspace.  A call
- * waits for the context's last launch, on whichever stream; calls that overlap otherwise (two
- * threads, two contexts, captured graphs) race: serialise them.
+ * PHX_ERR_CAPACITY, nothing enqueued.  Every call on one GPU shares that GPU's workspace, so
+ * calls that overlap on one GPU (two streams, two threads or two contexts) race: serialise them.
  * The parameter block is uploaded on `stream` when a load changed it (that call synchronises
- * `stream`). */
+ * `stream`, and a later upload or load that finds such a call behind it waits for the device). */
 phx_status phx_trace_noalloc(phx_ctx ctx, const phx_trace_args* args, void* stream);
 
 /* Launch shape of phx_trace / phx_trace_batched / phx_adjoint.  chunk_log2: photons per chunk =

@@ -81,6 +81,7 @@ struct phx_ctx_s {
     hipStream_t aux_stream = nullptr;       // optics stage of the chunk pipeline
     std::vector<hipEvent_t> pipe_ev;        // hand-off events of the chunk pipeline
     hipEvent_t order_ev = nullptr;          // end of the context's last launch (see order_begin)
+    bool unordered = false;                 // a trace without allocation may read the parameter block
     std::map<std::string, hipGraphExec_t> graphs;
     float autotune_ms = 0.0f;
     // adjoint workspace
@@ -400,15 +401,27 @@ phx_status set_device(phx_ctx c) {
     return e == hipSuccess ? PHX_OK : hip_fail(c, e, "hipSetDevice");
 }
 
+// Traces without allocation record no event (4 us of 16 for the smallest): what changes the parameter
+// block or a table waits for the device after one, which it does seldom.
+phx_status unordered_wait(phx_ctx c) {
+    if (!c->unordered) return PHX_OK;
+    const hipError_t e = hipDeviceSynchronize();
+    if (e != hipSuccess) return hip_fail(c, e, "hipDeviceSynchronize");
+    c->unordered = false;
+    return PHX_OK;
+}
+
 // Before a table that launches read is overwritten in place: the context's last launch is complete
 // (a copy of the null stream does not wait for other streams).
 phx_status order_wait(phx_ctx c) {
     const hipError_t e = hipEventSynchronize(c->order_ev);
-    return e == hipSuccess ? PHX_OK : hip_fail(c, e, "hipEventSynchronize");
+    return e == hipSuccess ? unordered_wait(c) : hip_fail(c, e, "hipEventSynchronize");
 }
 
 phx_status upload_params(phx_ctx c, hipStream_t stream) {
     if (!c->dirty) return PHX_OK;
+    const phx_status r = unordered_wait(c);
+    if (r != PHX_OK) return r;
     for (int k = 0; k < c->host.n_surf; ++k) {
         DevSurface& d = c->host.surf[k];
         d.coat = d.coating >= 0 && d.coating < c->host.n_coat
@@ -1262,8 +1275,8 @@ uint64_t make_plan(phx_ctx c, const phx_trace_args* a, const phx::Launch& L, uin
     return n;
 }
 
-// Launches of one context share its workspace and parameter block, so a launch waits for the one
-// before it, whichever stream that was on: order_end records an event behind a launch and
+// Launches of one context share its workspace and parameter block, so a launch (but for
+// phx_trace_noalloc's) waits for the one before it, whichever stream that was on: order_end records an event behind a launch and
 // order_begin, ahead of all that a call enqueues or frees, makes its stream wait for it (free on
 // the same stream; the record takes the host 4 us).  A stream that is being captured does neither:
 // its launches run when the graph does.
@@ -1481,9 +1494,10 @@ phx_status phx_trace_noalloc(phx_ctx c, const phx_trace_args* a, void* stream) {
         return fail(c, PHX_ERR_CAPACITY, "phx_trace_noalloc traces at most %d sources, not %d",
                     phx::kNoAllocMaxSources, L.n_src);
     if (!c->scratch) return fail(c, PHX_ERR_STATE, "no scratch address for this device");
-    r = order_begin(c, st);
+    // its workspace is not the context's; a changed parameter block waits for the launches that read it
+    if (c->dirty) r = order_begin(c, st);
     if (r != PHX_OK) return r;
-    if (L.total == 0) return upload_params(c, st);   // complete when it returns
+    if (L.total == 0) return upload_params(c, st);
     uint64_t chunk = 1024;
     const uint64_t max_chunk = 1ull << std::min(c->chunk_log2, phx::kNoAllocChunkLog2);
     while (chunk < L.total && chunk < max_chunk) chunk <<= 1;
@@ -1517,10 +1531,10 @@ phx_status phx_trace_noalloc(phx_ctx c, const phx_trace_args* a, void* stream) {
     r = upload_params(c, st);
     if (r != PHX_OK) return r;
     // every stage on the caller's stream, one buffer set, no timing events
+    c->unordered = true;
     const hipError_t e = phx::launch_trace(c->dparams, L, W, c->n_cu, c->cfg, st, phx::Pipe{},
                                            phx::Timing{});
-    const phx_status q = order_end(c, st);
-    return e == hipSuccess ? q : hip_fail(c, e, "trace kernel launch");
+    return e == hipSuccess ? PHX_OK : hip_fail(c, e, "trace kernel launch");
 }
 
 phx_status phx_trace_batched(phx_ctx c, const phx_trace_args* a, void* stream) {

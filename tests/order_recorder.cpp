@@ -1,10 +1,12 @@
 // The HIP runtime and the kernel launches that phx_api.cpp calls, replaced by a record of their
 // order, so that the host code's waits between streams can be checked without a GPU.
 //
-// Every launch, upload and synchronous copy is an operation with a number.  A stream knows the
-// operations that are complete when its next one starts: its own, those of the events that it waited
-// for, and those that the host had waited for when it issued the operation.  An operation that starts
-// without knowing an earlier one is written down: the two could overlap.
+// Every launch, upload and synchronous copy is an operation with a number, which reads and writes
+// the context's workspace, its parameter block or its tables.  A stream knows the operations that are
+// complete when its next one starts: its own, those of the events that it waited for, and those that
+// the host had waited for when it issued the operation.  An operation that starts without knowing an
+// earlier one with which it may not overlap is written down.  (The workspace of phx_trace_noalloc is not
+// a context's: the caller serialises those calls.)
 #include <hip/hip_runtime.h>
 
 #include <cstdlib>
@@ -22,24 +24,34 @@ typedef std::set<int> Known;
 std::map<void*, Known> g_stream, g_event;
 std::map<void*, bool> g_capturing;
 Known g_host;
-std::vector<std::string> g_ops;
+struct Op {
+    std::string name;
+    unsigned reads, writes;
+};
+std::vector<Op> g_ops;
+enum : unsigned { kWork = 1, kParams = 2, kTables = 4 };
 std::string g_overlaps;
 int g_resources, g_capture_events;   // allocations, frees, streams, events; event calls while capturing
 int g_handles;
 
 void join(Known& a, const Known& b) { a.insert(b.begin(), b.end()); }
 
-std::string label(int i) { return g_ops[(size_t)i] + "#" + std::to_string(i); }
+std::string label(int i) { return g_ops[(size_t)i].name + "#" + std::to_string(i); }
 
 void check(const Known& k) {
     const int id = (int)g_ops.size() - 1;
-    for (int j = 0; j < id; ++j)
+    const Op& o = g_ops.back();
+    for (int j = 0; j < id; ++j) {
+        const Op& p = g_ops[(size_t)j];
+        if (!((o.writes & (p.reads | p.writes)) | (o.reads & p.writes))) continue;
         if (!k.count(j)) g_overlaps += label(id) + " may overlap " + label(j) + "\n";
+    }
 }
 
-hipError_t on_stream(const char* name, hipStream_t s) {
+hipError_t on_stream(const char* name, hipStream_t s, unsigned reads = kParams | kTables,
+                     unsigned writes = kWork) {
     if (g_capturing[s]) return hipSuccess;   // runs when its graph does
-    g_ops.push_back(name);
+    g_ops.push_back({name, reads, writes});
     Known& k = g_stream[s];
     join(k, g_host);
     check(k);
@@ -48,7 +60,7 @@ hipError_t on_stream(const char* name, hipStream_t s) {
 }
 
 hipError_t on_host(const char* name) {   // complete when the call returns
-    g_ops.push_back(name);
+    g_ops.push_back({name, 0, kTables});
     check(g_host);
     g_host.insert((int)g_ops.size() - 1);
     return hipSuccess;
@@ -106,11 +118,11 @@ hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) {
 }
 hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t st) {
     std::memcpy(d, s, n);
-    return on_stream("upload", st);
+    return on_stream("upload", st, 0, kParams);
 }
 hipError_t hipMemsetAsync(void* d, int v, size_t n, hipStream_t st) {
     std::memset(d, v, n);
-    return on_stream("fill", st);
+    return on_stream("fill", st, 0, kTables);
 }
 hipError_t hipDeviceSynchronize() { host_waits_for_all(); return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t s) { join(g_host, g_stream[s]); return hipSuccess; }
@@ -159,10 +171,11 @@ hipError_t scratch_address(int, void** out) {
 }
 hipError_t launch_prefix(const DevSource*, int, int, uint64_t*, int32_t*, uint64_t, uint32_t,
                          hipStream_t s) {
-    return on_stream("prefix", s);
+    return on_stream("prefix", s, kTables, 0);
 }
-hipError_t launch_trace(const DevParams*, const Launch&, const Workspace&, int, const LaunchConfig&,
+hipError_t launch_trace(const DevParams*, const Launch&, const Workspace& W, int, const LaunchConfig&,
                         hipStream_t s, const Pipe&, const Timing&) {
+    if (W.buffers == 1) return on_stream("trace_noalloc", s, kParams | kTables, 0);
     return on_stream("trace", s);
 }
 hipError_t launch_adjoint(const DevParams*, const Launch&, const Workspace&, int,
@@ -170,13 +183,13 @@ hipError_t launch_adjoint(const DevParams*, const Launch&, const Workspace&, int
                           const Pipe&, const Timing&) {
     return on_stream("adjoint", s);
 }
-hipError_t launch_readout(const ReadoutJob&, hipStream_t s) { return on_stream("readout", s); }
+hipError_t launch_readout(const ReadoutJob&, hipStream_t s) { return on_stream("readout", s, 0); }
 hipError_t launch_moments(const unsigned long long*, int, double*, hipStream_t) { return hipSuccess; }
 hipError_t launch_seeds(const unsigned long long*, int, const double*, double*, hipStream_t s) {
-    return on_stream("seeds", s);
+    return on_stream("seeds", s, 0);
 }
 hipError_t launch_gradients(const float*, float4*, int, int, int, const double*, unsigned int*,
                             hipStream_t s) {
-    return on_stream("gradients", s);
+    return on_stream("gradients", s, 0, kTables);
 }
 }  // namespace phx
