@@ -290,6 +290,17 @@ constexpr int kGroupsPerUnit = 4;
 constexpr int stage_groups(const LaunchConfig& cfg, int per_cu) {
     return cfg.dynamic ? per_cu : kGroupsPerUnit * per_cu;
 }
+// Workgroups of the optics stage for len photons, in tiles of 256: all of them where each gets two tiles at
+// least, else half of them: one tile hardly pays for a workgroup's pixel window, which is cleared and added
+// to the image.  All / half / a quarter of 2048, in us: 4.3e5 photons through the paraboloid 40 / 33 / 32,
+// 1e6 59 / 48 / 51, 4e6 119 / 113 / 134; 1e6 through the full stack 413 / 386 / 413; 1.8e6 from 441 sources
+// through the telescope 251 / 279 / 326.
+constexpr uint64_t optics_groups(const LaunchConfig& cfg, int n_cu, uint64_t len) {
+    const uint64_t tiles = (len + kThreads - 1) / kThreads, width = (uint64_t)n_cu * cfg.back_per_cu;
+    const uint64_t most = (uint64_t)n_cu * stage_groups(cfg, cfg.back_per_cu);
+    const uint64_t g = tiles >= 2 * most || most == width ? most : most / 2;
+    return g < tiles ? g : tiles;
+}
 // Flags that select the sky and optics kernels carrying the per-photon physics beyond the core
 // path (the other instantiations hold none of its code).
 constexpr uint32_t kFrontExtra = PHX_F_DISPERSION | PHX_F_DOME | PHX_F_HALO | PHX_F_SECOND_KICK;

@@ -3094,9 +3094,7 @@ hipError_t launch_trace(const DevParams* dparams, const Launch& L, const Workspa
                            stream, (unsigned int*)W.tiles, 4 * n_chunks, 0u);
     S.run(n_chunks, cfg.dynamic != 0, [&](uint64_t c, hipStream_t bs) {
         const ChunkSpan& sp = W.plan[c];
-        const uint64_t want = (sp.len + kBlock - 1) / kBlock;
-        const uint64_t bcap = (uint64_t)n_cu * stage_groups(cfg, cfg.back_per_cu);
-        const dim3 bg((unsigned)(want < bcap ? want : bcap));
+        const dim3 bg((unsigned)optics_groups(cfg, n_cu, sp.len));
         unsigned long long* bt = cfg.dynamic ? W.tiles + 2 * c + 1 : nullptr;
         S.mark(2, 0, bs);
         const bool extra = (L.flags & kBackExtra) != 0, ghost = (L.flags & PHX_F_GHOSTS) != 0;
