@@ -173,7 +173,8 @@ __device__ __forceinline__ void zernike_poly(const double* c, double u, double v
 // What every passage needs of a surface, read with one scalar load and held in scalar registers.
 // The empty asm keeps the compiler from sinking each field's load to its first use, where the
 // wavefront would wait for it alone: with about ten such waits per surface, 45 % of the optics
-// kernel's wavefront time went into waiting (189 scalar loads per 64 photons; now 99, and 35 %).
+// kernel's wavefront time went into waiting (189 scalar loads per 64 photons; now 99, and 28 %
+// with four wavefronts per SIMD in place of three).
 struct SurfRegs {
     uint32_t bits;
     int32_t coating;
